@@ -336,10 +336,11 @@ size_t sdmm_tree_workspace_size(int64_t n_samples, int32_t max_leaves);
  * updated in place; sorted_out [device] float32[7][n_samples]: the samples by leaf, in
  * index order within a leaf; cell_offsets_out [device] int64[max_leaves + 1], of which
  * the first n_leaves + 1 entries are written; n_leaves_out, status_out [host] int32
- * (status_out may be NULL). The call synchronises the stream once per round. Means and
+ * (status_out may be NULL). The call synchronises the stream, at least twice: for the
+ * tree's counts and after each group of rounds it queues, the last time at its end. Means and
  * variances are FP64 sums over each leaf's samples. SDMM_EINVAL for bad arguments, or
  * when the tree's counts (read from the device) are out of range, in which case only the
- * workspace has been written. The call keeps one pinned 16-byte host buffer per host
+ * workspace has been written. The call keeps one pinned 32-byte host buffer per host
  * thread for the counts it reads back.
  */
 int sdmm_tree_refine(const sdmm_tree *tree, const float *samples, int64_t n_samples, int32_t split_threshold,
@@ -480,7 +481,7 @@ int sdmm_grad_to_params(int32_t n_cells, int32_t K, const double *L, const doubl
 #define SDMM_TIMER_GRAD 3    /* the adjoint pass of sdmm_fit_grad */
 #define SDMM_TIMER_ACCURATE 4 /* the second E-step pass of SDMM_FLAG_ACCURATE_SIGMA */
 #define SDMM_TIMER_PRODUCT 5  /* sdmm_product_sample */
-#define SDMM_TIMER_TREE 6     /* the first point-location launch of sdmm_tree_refine (every
+#define SDMM_TIMER_TREE 6     /* the point-location launch of sdmm_tree_refine (every
                                  sample walked from the root) */
 #define SDMM_TIMER_STEPWISE 7 /* the stepwise-EM kernel of SDMM_SCHED_STEPWISE */
 

@@ -4,15 +4,17 @@
 // arXiv 2111.13094, Sec. 4.2 "Refinement of the spatial kD-tree", Sec. 4.3
 // "Initialization").
 //
-// Refinement runs in rounds. Each round: every sample is located in the current tree;
-// the samples are ordered by leaf index, each leaf's samples contiguous and in index
-// order (a stable LSD radix sort in the first round, a stable partition of the previous
-// order after it); each leaf of the round with more than c samples gets its FP64 position
-// sums, minima and maxima from one work group (fixed reduction order); one work group
-// decides the splits in leaf order (a block prefix sum numbers the new nodes and leaves);
-// new leaves get copies of their parent's mixture and Robbins-Monro state. The host reads
-// the number of splits after each round and stops when a round makes none; the last
-// round's order is the final one.
+// Refinement: every sample is located in the tree once; a stable counting sort by leaf
+// moves the samples into leaf order as 16-byte records (position and index, direction and
+// weight); then rounds of splits work on the leaves' contiguous segments. Each round, for
+// every leaf of the round with more than c samples: the split from its FP64 position
+// statistics (fixed reduction order), the decisions in leaf order by one work group (block
+// prefix sums number the new nodes and leaves), and a stable partition of its segment,
+// which also forms the two children's statistics. Leaves that do not split are not
+// touched. No round waits for the host: the rounds' lists of leaves and work items live on
+// the device, the host queues a group of rounds ahead and reads back whether any leaf is
+// left. At the end the records are written out in the order of the leaf indices, and new
+// leaves get copies of their parent's mixture and Robbins-Monro state.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,9 +26,14 @@
 namespace sdmm {
 
 constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;                      // keys per thread per block
-constexpr int kSortTile = kSortThreads * kSortItems;  // keys per block
-constexpr int kRadixBits = 8, kRadix = 1 << kRadixBits;
+constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kSortItems = 16;                        // samples per thread per tile
+constexpr int kSortTile = kSortThreads * kSortItems;  // samples per tile
+constexpr int kDigitBits = 12, kMaxBins = 1 << kDigitBits;  // bins of one sorting pass
+constexpr int kScanRows = 32;                         // tiles per group of the tables' prefix sum
+constexpr int kChunkThreads = 512;
+constexpr int kChunkItems = 16;                             // records per thread per chunk
+constexpr int kChunk = kChunkThreads * kChunkItems;         // most records per chunk of a leaf
 constexpr int kMaxRounds = 64;
 
 struct TreePtrs {
@@ -84,6 +91,15 @@ __global__ void tree_init_kernel(TreePtrs t, int levels, double lo0, double lo1,
     }
 }
 
+// Work groups go to the eight XCDs in turn (group b to XCD b % 8), each XCD with its own
+// L2. The groups of one XCD take consecutive ranges of the output, so that a line
+// that two groups share is read or written in one L2, not in two.
+__device__ __forceinline__ int64_t xcd_block_order(int64_t b, int64_t nb)
+{
+    const int64_t x = b % 8, q = b / 8, per = nb / 8, extra = nb % 8;
+    return x * per + (x < extra ? x : extra) + q;
+}
+
 // ---------------------------------------------------------------------------------
 // point location: left where p[axis] < split, else right; child indices exceed their
 // parent's, so a walk ends within max_nodes steps. The oldest nodes, the top of the tree,
@@ -91,11 +107,10 @@ __global__ void tree_init_kernel(TreePtrs t, int levels, double lo0, double lo1,
 // kLocStaged: the whole tree while it has no more nodes than that), so a walk costs one
 // LDS read per level there; below them a node's axis, split, left child and leaf index
 // are loaded from global memory together (one memory round trip per level). Each thread
-// walks kLocPer samples side by side, so their reads overlap, and issues the next tile's
-// first loads before it walks the current one. After the first round a sample resumes
-// from the node it reached in the previous round (node_of), which is still its leaf
-// unless that leaf was split: its position is read only when it has to move, and its
-// node index is written only when it changes.
+// walks kLocPer samples side by side, so their reads overlap, and issues the next step's
+// positions before it walks the current ones. The work group also counts its tile's
+// samples per bin of the first sorting pass (the low kDigitBits bits of the leaf) in LDS
+// and writes the counts as one row of the sort's table.
 //
 // A staged entry holds the split rounded up to FP32: for an FP32 coordinate p and an FP64
 // split s, p < s exactly when p < f, f the least FP32 value not below s (every FP32 value
@@ -103,8 +118,9 @@ __global__ void tree_init_kernel(TreePtrs t, int levels, double lo0, double lo1,
 // branch with an FP32 comparison.
 // ---------------------------------------------------------------------------------
 constexpr int kLocThreads = 512;
-constexpr int kLocPer = 4;                       // samples per thread per tile
-constexpr int kLocTile = kLocThreads * kLocPer;  // samples per work group per tile
+constexpr int kLocPer = 4;                       // samples per thread per step
+constexpr int kLocTile = kLocThreads * kLocPer;  // samples per work group per step
+static_assert(kSortTile % kLocTile == 0, "a sorting tile is a whole number of steps");
 constexpr int kLocStaged = 4096;                 // nodes staged in LDS (32 KB)
 constexpr int kLocMaxGroups = 256 * 4;           // 4 work groups per CU
 constexpr int32_t kUnstaged = INT32_MIN;         // an inner node whose child index does not fit the code
@@ -121,33 +137,41 @@ __device__ __forceinline__ float round_up_f32(double s)
     return f;
 }
 
-// the loads that start a tile: the positions when every sample starts at the root, else
-// the nodes the samples reached before (a lane past the end loads the last sample's)
-template <bool FromRoot>
-__device__ __forceinline__ void loc_first_loads(const float* __restrict__ smp, const int32_t* __restrict__ node_of,
-                                                int64_t N, int64_t b, float (&p0)[kLocPer], float (&p1)[kLocPer],
-                                                float (&p2)[kLocPer], int32_t (&pn)[kLocPer])
+__device__ __forceinline__ void loc_loads(const float* __restrict__ smp, int64_t N, int64_t b, float (&p0)[kLocPer],
+                                          float (&p1)[kLocPer], float (&p2)[kLocPer])
 {
 #pragma unroll
-    for (int r = 0; r < kLocPer; ++r) {
+    for (int r = 0; r < kLocPer; ++r) {  // a lane past the end loads the last sample's
         const int64_t ic = min(b + r * kLocThreads, N - 1);
-        if (FromRoot) {
-            p0[r] = smp[3 * N + ic];
-            p1[r] = smp[4 * N + ic];
-            p2[r] = smp[5 * N + ic];
-        } else {
-            pn[r] = node_of[ic];
-        }
+        p0[r] = smp[3 * N + ic];
+        p1[r] = smp[4 * N + ic];
+        p2[r] = smp[5 * N + ic];
     }
 }
 
-template <bool FromRoot>
+// adds one to h[bin] for every valid lane; a wave whose valid lanes share the bin (samples
+// that arrive grouped by leaf) adds their number once, where the atomics would serialise
+__device__ __forceinline__ void count_bins(int32_t* h, int bin, bool valid)
+{
+    const uint64_t vm = __ballot(valid);
+    const int b0 = __builtin_amdgcn_readlane(bin, vm ? __builtin_ctzll(vm) : 0);
+    if (__all(!valid || bin == b0)) {
+        if (vm && (threadIdx.x & 63) == 0) atomicAdd(&h[b0], __popcll(vm));
+    } else if (valid) {
+        atomicAdd(&h[bin], 1);
+    }
+}
+
 __global__ __launch_bounds__(kLocThreads) void locate_kernel(TreePtrs t, const float* __restrict__ smp, int64_t N,
-                                                             int32_t* __restrict__ node_of,
-                                                             int32_t* __restrict__ leaf_of)
+                                                             int32_t* __restrict__ leaf_of, int32_t* __restrict__ hist,
+                                                             int n_tiles)
 {
     __shared__ StagedNode top[kLocStaged];
+    __shared__ int32_t h[kMaxBins];
     const int32_t ns = max(1, min(min(t.counts[0], t.max_nodes), kLocStaged));
+    // bins of the first sorting pass; a leaf index of a tree that the host will reject for
+    // its counts is kept inside them
+    const int32_t bins = max(1, min(min(t.counts[1], t.max_leaves), kMaxBins));
     {
         constexpr int kPer = kLocStaged / kLocThreads;
         const int jn = (ns + kLocThreads - 1) / kLocThreads;  // the same in every lane
@@ -170,636 +194,896 @@ __global__ __launch_bounds__(kLocThreads) void locate_kernel(TreePtrs t, const f
             if (k < ns) top[k] = StagedNode{round_up_f32(sp[j]), code};
         }
     }
+    for (int b = threadIdx.x; b < bins; b += kLocThreads) h[b] = 0;
     __syncthreads();
     // a lane past the end walks the last sample's path again and stores nothing
-    const int64_t stride = (int64_t)gridDim.x * kLocTile;
-    int64_t base = (int64_t)blockIdx.x * kLocTile + threadIdx.x;
-    float p0[kLocPer], p1[kLocPer], p2[kLocPer];  // first loads of the next tile
-    int32_t pn[kLocPer];
-    if (base < N) loc_first_loads<FromRoot>(smp, node_of, N, base, p0, p1, p2, pn);
-    for (; base < N; base += stride) {
-        int32_t n[kLocPer], n0[kLocPer];
-        float q0[kLocPer], q1[kLocPer], q2[kLocPer];
-        if (FromRoot) {
+    constexpr int kSteps = kSortTile / kLocTile;
+    float p0[kLocPer], p1[kLocPer], p2[kLocPer];  // positions of the next step
+    if ((int)blockIdx.x < n_tiles)
+        loc_loads(smp, N, (int64_t)blockIdx.x * kSortTile + threadIdx.x, p0, p1, p2);
+    for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        for (int step = 0; step < kSteps; ++step) {
+            const int64_t base = (int64_t)tile * kSortTile + step * kLocTile + threadIdx.x;
+            int32_t n[kLocPer];
+            float q0[kLocPer], q1[kLocPer], q2[kLocPer];
 #pragma unroll
             for (int r = 0; r < kLocPer; ++r) {
-                n0[r] = 0;
+                n[r] = 0;
                 q0[r] = p0[r];
                 q1[r] = p1[r];
                 q2[r] = p2[r];
             }
-        } else {
-#pragma unroll
-            for (int r = 0; r < kLocPer; ++r) n0[r] = pn[r];
-        }
-        if (base + stride < N) loc_first_loads<FromRoot>(smp, node_of, N, base + stride, p0, p1, p2, pn);
-        if (!FromRoot) {
-            // a sample at an inner node moves: only then is its position read
-            int32_t c[kLocPer];
-#pragma unroll
-            for (int r = 0; r < kLocPer; ++r) c[r] = top[min(n0[r], ns - 1)].code;
-#pragma unroll
-            for (int r = 0; r < kLocPer; ++r) {
-                const bool staged = n0[r] < ns && c[r] != kUnstaged;
-                const bool inner = staged ? c[r] >= 0 : t.axis[n0[r]] >= 0;
-                const int64_t ic = min(base + r * kLocThreads, N - 1);
-                q0[r] = q1[r] = q2[r] = 0.0f;
-                if (inner) {
-                    q0[r] = smp[3 * N + ic];
-                    q1[r] = smp[4 * N + ic];
-                    q2[r] = smp[5 * N + ic];
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kLocPer; ++r) n[r] = n0[r];
-        // the staged levels: a step per LDS read
-        for (int32_t s = 0; s <= ns; ++s) {
-            bool more = false;
-            StagedNode e[kLocPer];
-#pragma unroll
-            for (int r = 0; r < kLocPer; ++r) e[r] = top[min(n[r], ns - 1)];
-#pragma unroll
-            for (int r = 0; r < kLocPer; ++r) {
-                const bool go = n[r] < ns && e[r].code >= 0;
-                const float t01 = (e[r].code & 1) ? q1[r] : q0[r];
-                const float pa = (e[r].code & 2) ? q2[r] : t01;
-                const int32_t to = (e[r].code >> 2) + (pa < e[r].split ? 0 : 1);
-                n[r] = go ? to : n[r];
-                more |= go;
-            }
-            if (!more) break;
-        }
-        // the levels below: a step per global round trip (only where a walk left the
-        // staged nodes, so that the other waves never wait for the next tile's loads)
-        int32_t lv[kLocPer];
-        bool staged[kLocPer], below = false;
-#pragma unroll
-        for (int r = 0; r < kLocPer; ++r) {
-            const int32_t c = top[min(n[r], ns - 1)].code;
-            staged[r] = n[r] < ns && c != kUnstaged;  // then a leaf
-            lv[r] = -c - 1;
-            below |= !staged[r];
-        }
-        if (below) {
-            int32_t ax[kLocPer], lf[kLocPer];
-            double sp[kLocPer];
-#pragma unroll
-            for (int r = 0; r < kLocPer; ++r) {
-                ax[r] = -1;
-                lf[r] = -1;
-                sp[r] = 0.0;
-                if (!staged[r]) {
-                    ax[r] = t.axis[n[r]];
-                    lf[r] = t.left[n[r]];
-                    sp[r] = t.split[n[r]];
-                    lv[r] = t.leaf[n[r]];
-                }
-            }
-            for (int32_t s = 0; s < t.max_nodes; ++s) {
-                // the loads above and below complete together at these empty statements
-                // (the compiler would otherwise issue the later ones only after the axis
-                // came back)
-#pragma unroll
-                for (int r = 0; r < kLocPer; ++r)
-                    asm volatile("" ::"v"(ax[r]), "v"(lf[r]), "v"(sp[r]), "v"(lv[r]));
+            const int64_t next = step + 1 < kSteps ? base + kLocTile
+                                                   : (int64_t)(tile + (int)gridDim.x) * kSortTile + threadIdx.x;
+            if (step + 1 < kSteps || tile + (int)gridDim.x < n_tiles) loc_loads(smp, N, next, p0, p1, p2);
+            // the staged levels: a step per LDS read
+            for (int32_t s = 0; s <= ns; ++s) {
                 bool more = false;
+                StagedNode e[kLocPer];
+#pragma unroll
+                for (int r = 0; r < kLocPer; ++r) e[r] = top[min(n[r], ns - 1)];
 #pragma unroll
                 for (int r = 0; r < kLocPer; ++r) {
-                    if (ax[r] >= 0) {
-                        const float pa = ax[r] == 0 ? q0[r] : (ax[r] == 1 ? q1[r] : q2[r]);
-                        n[r] = (double)pa < sp[r] ? lf[r] : lf[r] + 1;
+                    const bool go = n[r] < ns && e[r].code >= 0;
+                    const float t01 = (e[r].code & 1) ? q1[r] : q0[r];
+                    const float pa = (e[r].code & 2) ? q2[r] : t01;
+                    const int32_t to = (e[r].code >> 2) + (pa < e[r].split ? 0 : 1);
+                    n[r] = go ? to : n[r];
+                    more |= go;
+                }
+                if (!more) break;
+            }
+            // the levels below: a step per global round trip (only where a walk left the
+            // staged nodes, so that the other waves never wait for the next tile's loads)
+            int32_t lv[kLocPer];
+            bool staged[kLocPer], below = false;
+#pragma unroll
+            for (int r = 0; r < kLocPer; ++r) {
+                const int32_t c = top[min(n[r], ns - 1)].code;
+                staged[r] = n[r] < ns && c != kUnstaged;  // then a leaf
+                lv[r] = -c - 1;
+                below |= !staged[r];
+            }
+            if (below) {
+                int32_t ax[kLocPer], lf[kLocPer];
+                double sp[kLocPer];
+#pragma unroll
+                for (int r = 0; r < kLocPer; ++r) {
+                    ax[r] = -1;
+                    lf[r] = -1;
+                    sp[r] = 0.0;
+                    if (!staged[r]) {
                         ax[r] = t.axis[n[r]];
                         lf[r] = t.left[n[r]];
                         sp[r] = t.split[n[r]];
                         lv[r] = t.leaf[n[r]];
-                        more = true;
                     }
                 }
-                if (!more) break;
+                for (int32_t s = 0; s < t.max_nodes; ++s) {
+                    // the loads above and below complete together at these empty statements
+                    // (the compiler would otherwise issue the later ones only after the axis
+                    // came back)
+#pragma unroll
+                    for (int r = 0; r < kLocPer; ++r)
+                        asm volatile("" ::"v"(ax[r]), "v"(lf[r]), "v"(sp[r]), "v"(lv[r]));
+                    bool more = false;
+#pragma unroll
+                    for (int r = 0; r < kLocPer; ++r) {
+                        if (ax[r] >= 0) {
+                            const float pa = ax[r] == 0 ? q0[r] : (ax[r] == 1 ? q1[r] : q2[r]);
+                            n[r] = (double)pa < sp[r] ? lf[r] : lf[r] + 1;
+                            ax[r] = t.axis[n[r]];
+                            lf[r] = t.left[n[r]];
+                            sp[r] = t.split[n[r]];
+                            lv[r] = t.leaf[n[r]];
+                            more = true;
+                        }
+                    }
+                    if (!more) break;
+                }
+            }
+
+#pragma unroll
+            for (int r = 0; r < kLocPer; ++r) {
+                const int64_t i = base + r * kLocThreads;
+                if (i < N) leaf_of[i] = lv[r];
+                const int bin = min(max(lv[r], 0) & (kMaxBins - 1), bins - 1);
+                count_bins(h, bin, i < N);
             }
         }
-#pragma unroll
-        for (int r = 0; r < kLocPer; ++r) {
-            const int64_t i = base + r * kLocThreads;
-            if (i >= N) continue;
-            if (FromRoot || n[r] != n0[r]) node_of[i] = n[r];
-            leaf_of[i] = lv[r];
+        __syncthreads();
+        for (int b = threadIdx.x; b < bins; b += kLocThreads) {
+            hist[(int64_t)tile * bins + b] = h[b];
+            h[b] = 0;
         }
+        __syncthreads();
     }
 }
 
 // ---------------------------------------------------------------------------------
-// stable LSD radix sort of (leaf index, sample index) by leaf index, 8 bits per pass
+// Stable counting sort by leaf, kDigitBits bits of the leaf index per pass (one pass up to
+// 4096 leaves): a table of counts with one row per tile (written by the location for the
+// first pass), its prefix sums down the tiles and across the bins, and the move. The
+// samples are moved whole, as two 16-byte records: position and index, direction and
+// weight. A sample's record then lands in a full sector, and runs of one tile's samples of
+// a leaf are contiguous; moving indices only left a gather of 28 bytes in 4-byte pieces
+// from 7 random lines each to the end (2.04 ms of the 12.5 ms of a 16.6M-sample refinement
+// in path order), and every round's partition and statistics read through the
+// permutation as well.
 // ---------------------------------------------------------------------------------
+
+// counts per tile and bin of the keys' digit (passes after the first)
+__global__ __launch_bounds__(kSortThreads) void tile_hist_kernel(const int32_t* __restrict__ keys, int64_t N, int shift,
+                                                                 int bins, int32_t* __restrict__ hist)
+{
+    __shared__ int32_t h[kMaxBins];
+    for (int b = threadIdx.x; b < bins; b += kSortThreads) h[b] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * kSortTile + threadIdx.x;
+    int32_t kv[kSortItems];  // the thread's keys, loaded together
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it) kv[it] = keys[min(base + it * kSortThreads, N - 1)];
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it)
+        count_bins(h, min((kv[it] >> shift) & (kMaxBins - 1), bins - 1), base + it * kSortThreads < N);
+    __syncthreads();
+    for (int b = threadIdx.x; b < bins; b += kSortThreads) hist[(int64_t)blockIdx.x * bins + b] = h[b];
+}
+
+// exclusive prefix sum of each bin down the kScanRows tiles of a group (in place), and the
+// group's total; consecutive threads take consecutive bins, so every row is read whole
+__global__ __launch_bounds__(256) void scan_group_kernel(int32_t* __restrict__ hist, int n_tiles, int bins,
+                                                         int32_t* __restrict__ gsum)
+{
+    const int b = blockIdx.x * 256 + threadIdx.x, g = blockIdx.y;
+    if (b >= bins) return;
+    const int t0 = g * kScanRows;
+    int32_t v[kScanRows];
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) v[i] = t0 + i < n_tiles ? hist[(int64_t)(t0 + i) * bins + b] : 0;
+    int32_t run = 0;
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) {
+        if (t0 + i < n_tiles) hist[(int64_t)(t0 + i) * bins + b] = run;
+        run += v[i];
+    }
+    gsum[(int64_t)g * bins + b] = run;
+}
+
+// exclusive prefix sum of each bin over the groups (in place), and the bin's total
+__global__ __launch_bounds__(64) void scan_bins_kernel(int32_t* __restrict__ gsum, int n_groups, int bins,
+                                                       int32_t* __restrict__ total)
+{
+    const int b = blockIdx.x * 64 + threadIdx.x;
+    if (b >= bins) return;
+    constexpr int U = 16;
+    int32_t run = 0;
+    for (int g0 = 0; g0 < n_groups; g0 += U) {
+        int32_t v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) v[i] = g0 + i < n_groups ? gsum[(int64_t)(g0 + i) * bins + b] : 0;
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (g0 + i < n_groups) gsum[(int64_t)(g0 + i) * bins + b] = run;
+            run += v[i];
+        }
+    }
+    total[b] = run;
+}
+
+// exclusive prefix sum over a work group of 1024 threads
+template <typename T>
+__device__ __forceinline__ T block_scan_1024(T v, T* wsum, T& total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    T x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    T before = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const T s = wsum[q];
+        before += q < w ? s : T(0);
+        all += s;
+    }
+    total = all;
+    __syncthreads();
+    return before + x - v;
+}
+
+// A leaf of a round: its segment of the records (in buffer src), its chunks (work items
+// item0 .. item0 + nch - 1) and the partial statistics to sum for it (pn of them from
+// pfirst, on one side of their records' split).
+struct Entry {
+    int32_t leaf, start, count, src, item0, nch, pfirst, pn2;  // pn2 = 2 pn + side
+};
+
+// statistics of a chunk's samples, or of those on one side of its split
+struct Part {
+    double s1[3], sq[3];
+    float mn[3], mx[3];
+};
+
+// the device's control words: entries and work items of the lists of even and odd rounds,
+// the status bits, the number of leaves
+constexpr int kCtlEntries = 0, kCtlItems = 2, kCtlStatus = 4, kCtlLeaves = 5, kCtlWords = 8;
+
+// whether no leaf is left to split: the list that the last of the queued rounds wrote is
+// empty (done < 2: its parity), or the limit of the rounds is reached (done = 2)
+__device__ __forceinline__ bool finished(const int32_t* __restrict__ ctl, int done)
+{
+    return done == 2 || ctl[kCtlEntries + done] == 0;
+}
+
+struct LeafTabs {
+    int32_t *start, *count, *par, *origin;  // segment and its buffer; the leaf whose mixture it copies
+};
+
+struct RoundBufs {
+    Entry* entries[2];
+    int32_t *items[2], *rtot[2];  // entry of each work item; samples on the right per entry
+    Part* parts[2];               // per side: parts[.][side * max_items + item]
+    int32_t *item_right, *flags, *ax;
+    double* split;
+    int32_t max_items;
+};
+
+__device__ __forceinline__ int32_t chunks_of(int32_t count) { return (count + kChunk - 1) / kChunk; }
+
+// One work group: a pass's bins get their bases (exclusive prefix sum of the totals); with
+// leaves, every bin is a leaf and the leaf tables are set from them (else from the starts
+// that starts_kernel wrote), and the first round's list takes every leaf with more than c
+// samples, in leaf order.
+__global__ __launch_bounds__(1024) void base_kernel(int32_t* __restrict__ total, int bins, int leaves, int32_t L, int32_t c,
+                                                    LeafTabs lt, RoundBufs rb, int32_t* __restrict__ ctl)
+{
+    __shared__ int64_t ws[16];
+    __shared__ int32_t ws32[16];
+    const int tid = threadIdx.x;
+    if (bins > 0) {
+        int32_t run = 0;
+        for (int b0 = 0; b0 < bins; b0 += 1024) {
+            const int b = b0 + tid;
+            const int32_t v = b < bins ? total[b] : 0;
+            int32_t all;
+            const int32_t x = run + block_scan_1024(v, ws32, all);
+            if (b < bins) total[b] = x;
+            if (leaves && b < L) {
+                lt.start[b] = x;
+                lt.count[b] = v;
+            }
+            run += all;
+        }
+    }
+    if (!leaves) return;
+    if (bins == 0) {
+        for (int32_t l = tid; l < L; l += 1024) lt.count[l] = lt.start[l + 1] - lt.start[l];
+    }
+    __syncthreads();
+    int32_t e0 = 0, i0 = 0;
+    for (int32_t l0 = 0; l0 < L; l0 += 1024) {
+        const int32_t l = l0 + tid;
+        const int32_t n = l < L ? lt.count[l] : 0;
+        if (l < L) {
+            lt.par[l] = 0;
+            lt.origin[l] = l;
+        }
+        const bool in = n > c;
+        const int32_t nch = in ? chunks_of(n) : 0;
+        int64_t all;
+        const int64_t x = block_scan_1024(((int64_t)(in ? 1 : 0) << 32) | nch, ws, all);
+        if (in) {
+            const int32_t e = e0 + (int32_t)(x >> 32), it = i0 + (int32_t)x;
+            rb.entries[0][e] = Entry{l, lt.start[l], n, 0, it, nch, it, 2 * nch};
+            rb.rtot[0][e] = 0;
+            for (int32_t q = 0; q < nch; ++q) rb.items[0][it + q] = e;
+        }
+        e0 += (int32_t)(all >> 32);
+        i0 += (int32_t)all;
+    }
+    if (tid == 0) {
+        ctl[kCtlEntries] = e0;
+        ctl[kCtlItems] = i0;
+        ctl[kCtlEntries + 1] = ctl[kCtlItems + 1] = 0;
+        ctl[kCtlStatus] = 0;
+        ctl[kCtlLeaves] = L;
+    }
+}
+
+// start[l] = first sorted position of leaf l (start[L] = N), from the sorted keys (more
+// leaves than one pass has bins)
+__global__ void starts_kernel(const int32_t* __restrict__ keys, int64_t N, int32_t L, int32_t* __restrict__ start)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    const int32_t k = keys[i], kp = i > 0 ? keys[i - 1] : -1;
+    for (int32_t l = kp + 1; l <= k; ++l) start[l] = (int32_t)i;
+    if (i == N - 1)
+        for (int32_t l = k + 1; l <= L; ++l) start[l] = (int32_t)N;
+}
+
 // the valid lanes of the wave whose digit equals this lane's (meaningful for valid lanes):
 // one comparison when every valid lane holds the same digit, as in runs of samples of one
 // leaf, else one ballot per digit bit
-__device__ __forceinline__ uint64_t digit_peers(int digit, bool valid)
+__device__ __forceinline__ uint64_t digit_peers(int digit, bool valid, int bits)
 {
     const uint64_t vm = __ballot(valid);
     const int d0 = __builtin_amdgcn_readfirstlane(digit);
     if (__all(!valid || digit == d0)) return vm;
     uint64_t peers = vm;
-#pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
-        const uint64_t m = __ballot((digit >> b) & 1);
-        peers &= ((digit >> b) & 1) ? m : ~m;
+    for (int b = 0; b < bits; ++b) {
+        const bool on = (digit >> b) & 1;
+        const uint64_t m = __ballot(on);
+        peers &= on ? m : ~m;
     }
     return peers;
 }
 
-__global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const int32_t* __restrict__ keys, int64_t N,
-                                                                  int shift, int32_t* __restrict__ hist, int B)
+// Each work group moves its tile, wave w the tile's samples [1024 w, 1024 (w + 1)) in
+// order: first every sample's rank among the wave's samples of its digit (ballots within
+// 64 samples, a running count per digit in the wave's own row of LDS across them), then
+// the rows' prefix over the waves, then the moves, four samples per thread in flight. Work
+// groups of one XCD take consecutive tiles, so that a line that two tiles' runs share is
+// written in one L2.
+template <bool FromSamples>
+__global__ __launch_bounds__(kSortThreads) void scatter_kernel(
+    const float* __restrict__ smp, const float4* __restrict__ pin, const float4* __restrict__ qin,
+    const int32_t* __restrict__ kin, int64_t N, int shift, int bins, int bits, const int32_t* __restrict__ hist,
+    const int32_t* __restrict__ gsum, const int32_t* __restrict__ base, float4* __restrict__ pout,
+    float4* __restrict__ qout, int32_t* __restrict__ kout)
 {
-    __shared__ int32_t h[kRadix];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    // lanes with equal digits (found by 8 ballots) add their count once: the keys of a
-    // tile are mostly equal when the samples arrive grouped, and LDS atomics on one
-    // address serialise
-    const int lane = threadIdx.x & 63;
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    int32_t kv[kSortItems];  // the thread's keys, loaded together
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = base + (int64_t)it * kSortThreads + threadIdx.x;
-        kv[it] = i < N ? keys[i] : 0;
-    }
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = base + (int64_t)it * kSortThreads + threadIdx.x;
-        const bool valid = i < N;
-        const int digit = valid ? (kv[it] >> shift) & (kRadix - 1) : 0;
-        const uint64_t peers = digit_peers(digit, valid);
-        if (valid && (peers & lt) == 0) atomicAdd(&h[digit], __popcll(peers));
-    }
-    __syncthreads();
-    hist[(int64_t)threadIdx.x * B + blockIdx.x] = h[threadIdx.x];
-}
-
-// Exclusive prefix sum of n int32 counts in three launches: tile sums (kScanTile
-// entries per work group), an exclusive scan of the tile sums by one work group, and the
-// scan of each tile from its base.
-constexpr int kScanPer = 16;
-constexpr int kScanTile = 256 * kScanPer;
-
-__device__ __forceinline__ int32_t block_exclusive_scan_256(int32_t v, int32_t& total)
-{
-    __shared__ int32_t wsum[4];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    int32_t before = 0;
-    for (int q = 0; q < w; ++q) before += wsum[q];
-    total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-    __syncthreads();
-    return before + x - v;
-}
-
-__global__ __launch_bounds__(256) void scan_tile_sums_kernel(const int32_t* __restrict__ v, int64_t n,
-                                                             int32_t* __restrict__ sums)
-{
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-    int32_t s = 0;
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q)
-        if (base + q < n) s += v[base + q];
-    int32_t total;
-    (void)block_exclusive_scan_256(s, total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(1024) void scan_sums_kernel(int32_t* __restrict__ v, int64_t n)
-{
-    __shared__ int64_t part[1024];
-    const int64_t chunk = (n + 1023) / 1024;
-    const int64_t a = min(n, (int64_t)threadIdx.x * chunk), b = min(n, a + chunk);
-    int64_t s = 0;
-    for (int64_t i = a; i < b; ++i) s += v[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {  // inclusive scan of the partial sums
-        const int64_t add = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    int64_t run = part[threadIdx.x] - s;
-    for (int64_t i = a; i < b; ++i) {
-        const int64_t c = v[i];
-        v[i] = (int32_t)run;
-        run += c;
-    }
-}
-
-__global__ __launch_bounds__(256) void scan_apply_kernel(int32_t* __restrict__ v, int64_t n,
-                                                         const int32_t* __restrict__ sums)
-{
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-    int32_t x[kScanPer];
-    int32_t s = 0;
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) {
-        x[q] = base + q < n ? v[base + q] : 0;
-        s += x[q];
-    }
-    int32_t total;
-    int32_t run = sums[blockIdx.x] + block_exclusive_scan_256(s, total);
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) {
-        if (base + q < n) v[base + q] = run;
-        run += x[q];
-    }
-}
-
-// Each block scatters its tile in index order: per 256-key step, a key's rank among the
-// equal digits of its wave comes from 8 ballots (the tile's keys and values are loaded up
-// front), the waves of the block are ordered by
-// per-wave digit counts in LDS, and a running base per digit carries over the steps.
-__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(const int32_t* __restrict__ kin,
-                                                                     const int32_t* __restrict__ vin, int64_t N,
-                                                                     int shift, const int32_t* __restrict__ hist,
-                                                                     int B, int32_t* __restrict__ kout,
-                                                                     int32_t* __restrict__ vout)
-{
-    constexpr int W = kSortThreads / 64;
-    __shared__ int32_t base[kRadix];
-    __shared__ int32_t wcount[W][kRadix];
+    extern __shared__ int32_t lds[];
+    int32_t* gbase = lds;                                       // [bins]
+    uint16_t* wc = reinterpret_cast<uint16_t*>(lds + bins);     // [kSortWaves][bins]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    base[tid] = hist[(int64_t)tid * B + blockIdx.x];
-    for (int q = 0; q < W; ++q) wcount[q][tid] = 0;
+    const int tile = (int)xcd_block_order(blockIdx.x, gridDim.x);
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const int64_t first = (int64_t)tile * kSortTile + w * (64 * kSortItems) + lane;
+    int32_t kv[kSortItems], rank[kSortItems];
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it) kv[it] = kin[min(first + it * 64, N - 1)];
+    for (int b = tid; b < bins; b += kSortThreads) {
+        gbase[b] = base[b] + gsum[(int64_t)(tile / kScanRows) * bins + b] + hist[(int64_t)tile * bins + b];
+#pragma unroll
+        for (int q = 0; q < kSortWaves; ++q) wc[q * bins + b] = 0;
+    }
     __syncthreads();
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int64_t tile = (int64_t)blockIdx.x * kSortTile;
-    // the thread's keys and values, loaded together before the barriers of the steps
-    int32_t kv[kSortItems], vv[kSortItems];
+    volatile uint16_t* row = wc + w * bins;
 #pragma unroll
     for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile + (int64_t)it * kSortThreads + tid;
-        const bool valid = i < N;
-        kv[it] = valid ? kin[i] : 0;
-        vv[it] = valid ? (vin ? vin[i] : (int32_t)i) : 0;
+        const bool valid = first + it * 64 < N;
+        const int digit = min((kv[it] >> shift) & (kMaxBins - 1), bins - 1);
+        const uint64_t peers = digit_peers(digit, valid, bits);
+        const int before = row[digit];
+        rank[it] = before + __popcll(peers & lt);
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (peers & lt) == 0) row[digit] = (uint16_t)(before + __popcll(peers));
+        __builtin_amdgcn_wave_barrier();
     }
+    __syncthreads();
+    for (int b = tid; b < bins; b += kSortThreads) {
+        int run = 0;
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile + (int64_t)it * kSortThreads + tid;
-        const bool valid = i < N;
-        const int32_t key = kv[it];
-        const int32_t val = vv[it];
-        const int digit = (key >> shift) & (kRadix - 1);
-        const uint64_t peers = digit_peers(digit, valid);
-        const int rank = __popcll(peers & lt);
-        if (valid && rank == 0) wcount[w][digit] = __popcll(peers);
-        __syncthreads();
-        if (valid) {
-            int32_t before = base[digit];
-            for (int q = 0; q < w; ++q) before += wcount[q][digit];
-            const int64_t dst = (int64_t)before + rank;
-            kout[dst] = key;
-            vout[dst] = val;
+        for (int q = 0; q < kSortWaves; ++q) {
+            const int v = wc[q * bins + b];
+            wc[q * bins + b] = (uint16_t)run;
+            run += v;
         }
-        __syncthreads();
-        int32_t tot = 0;
-        for (int q = 0; q < W; ++q) {
-            tot += wcount[q][tid];
-            wcount[q][tid] = 0;
-        }
-        base[tid] += tot;
-        __syncthreads();
     }
-}
-
-// ---------------------------------------------------------------------------------
-// the order by leaf after a round's splits follows from the previous round's: a sample
-// stays in its leaf, or goes to the left child, which keeps the parent's leaf index, or to
-// the right child, whose index is at least the previous leaf count and grows with the
-// parent's. So the samples now below that count keep their relative order, and the others
-// follow them in theirs: a stable partition of the previous permutation (two launches and
-// a one-group scan of the tiles' counts) takes the place of the radix sort.
-// ---------------------------------------------------------------------------------
-
-// cnt[b] = the samples of tile b (in the previous order) now in a leaf >= L_old; cnt[B] = 0
-__global__ __launch_bounds__(kSortThreads) void part_count_kernel(const int32_t* __restrict__ perm,
-                                                                  const int32_t* __restrict__ leaf_of, int64_t N,
-                                                                  int32_t L_old, int32_t* __restrict__ cnt, int B)
-{
-    const int64_t tile = (int64_t)blockIdx.x * kSortTile;
-    int32_t pv[kSortItems];
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile + (int64_t)it * kSortThreads + threadIdx.x;
-        pv[it] = perm[min(i, N - 1)];
-    }
-    int32_t c = 0;
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile + (int64_t)it * kSortThreads + threadIdx.x;
-        c += (i < N && leaf_of[pv[it]] >= L_old) ? 1 : 0;
-    }
-    int32_t total;
-    (void)block_exclusive_scan_256(c, total);
-    if (threadIdx.x == 0) {
-        cnt[blockIdx.x] = total;
-        if (blockIdx.x == 0) cnt[B] = 0;
-    }
-}
-
-// after the exclusive scan of cnt (cnt[B] = all such samples): position j of the previous
-// order goes to j - t_j, or to N - cnt[B] + t_j if its new leaf is >= L_old, t_j being the
-// number of such samples before j
-__global__ __launch_bounds__(kSortThreads) void part_scatter_kernel(const int32_t* __restrict__ perm,
-                                                                    const int32_t* __restrict__ leaf_of, int64_t N,
-                                                                    int32_t L_old, const int32_t* __restrict__ cnt,
-                                                                    int B, int32_t* __restrict__ kout,
-                                                                    int32_t* __restrict__ vout)
-{
-    constexpr int W = kSortThreads / 64;
-    __shared__ int32_t wt[W];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int64_t tile = (int64_t)blockIdx.x * kSortTile;
-    const int64_t first_up = N - (int64_t)cnt[B];
-    int32_t pv[kSortItems], kv[kSortItems];
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile + (int64_t)it * kSortThreads + threadIdx.x;
-        pv[it] = perm[min(i, N - 1)];
-    }
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) kv[it] = leaf_of[pv[it]];
-    int64_t run = cnt[blockIdx.x];  // such samples before the current step
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const int64_t i = tile + (int64_t)it * kSortThreads + threadIdx.x;
-        const bool valid = i < N, up = valid && kv[it] >= L_old;
-        const uint64_t m = __ballot(up);
-        if (lane == 0) wt[w] = __popcll(m);
-        __syncthreads();
-        int64_t tj = run + __popcll(m & lt);
-        int32_t all = 0;
-#pragma unroll
-        for (int q = 0; q < W; ++q) {
-            tj += q < w ? wt[q] : 0;
-            all += wt[q];
-        }
-        if (valid) {
-            const int64_t dst = up ? first_up + tj : i - tj;
-            kout[dst] = kv[it];
-            vout[dst] = pv[it];
-        }
-        run += all;
-        __syncthreads();
-    }
-}
-
-// off[l] = first sorted position of leaf l (off[L] = N), for leaves 0..L
-__global__ void segment_kernel(const int32_t* __restrict__ keys, int64_t N, int32_t L, int64_t* __restrict__ off)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (N == 0) {
-        if (i <= L) off[i] = 0;
-        return;
-    }
-    if (i >= N) return;
-    const int32_t k = keys[i], kp = i > 0 ? keys[i - 1] : -1;
-    for (int32_t l = kp + 1; l <= k; ++l) off[l] = i;
-    if (i == N - 1)
-        for (int32_t l = k + 1; l <= L; ++l) off[l] = N;
-}
-
-// ---------------------------------------------------------------------------------
-// split statistics: one work group of kStatThreads per leaf of the round with more than c
-// samples (16 waves, so that the few large leaves of the first rounds keep enough loads in
-// flight); FP64 sums reduced in a fixed order (lanes by butterfly, then the waves in order)
-// ---------------------------------------------------------------------------------
-constexpr int kStatThreads = 1024;
-
-__global__ __launch_bounds__(kStatThreads) void split_stats_kernel(const float* __restrict__ smp, int64_t N,
-                                                          const int32_t* __restrict__ perm,
-                                                          const int64_t* __restrict__ off, int32_t L, int32_t c,
-                                                          const int32_t* __restrict__ act, int32_t* __restrict__ want,
-                                                          int32_t* __restrict__ sax, double* __restrict__ spos)
-{
-    constexpr int W = kStatThreads / 64;
-    __shared__ double ls1[W][3], lsq[W][3];
-    __shared__ float lmn[W][3], lmx[W][3];
-    const int l = blockIdx.x;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (l >= L) return;
-    const int64_t a = off[l], b = off[l + 1], M = b - a;
-    if (!act[l] || M <= c) {
-        if (threadIdx.x == 0) want[l] = 0;
-        return;
-    }
-    double s1[3] = {0, 0, 0}, sq[3] = {0, 0, 0};
-    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    // the positions are gathered through the sort's permutation: four of a thread's
-    // samples are loaded together (indices clamped into the leaf, so every load is in
-    // bounds) and then added in the thread's sample order
+    __syncthreads();
     constexpr int U = 4;
-    int32_t idx[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) idx[u] = perm[min(a + threadIdx.x + u * kStatThreads, b - 1)];
-    for (int64_t j0 = a + threadIdx.x; j0 < b; j0 += U * kStatThreads) {
-        float xs[U][3];
+    for (int i0 = 0; i0 < kSortItems; i0 += U) {
+        float4 p[U], q[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) xs[u][d] = smp[(3 + d) * N + idx[u]];
-        // the next step's indices are on their way while these positions are added
-        const int64_t jn = j0 + U * kStatThreads;
-        if (jn < b) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) idx[u] = perm[min(jn + u * kStatThreads, b - 1)];
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = min(first + (i0 + u) * 64, N - 1);
+            if constexpr (FromSamples) {
+                p[u] = make_float4(smp[3 * N + i], smp[4 * N + i], smp[5 * N + i], 0.0f);
+                q[u] = make_float4(smp[i], smp[N + i], smp[2 * N + i], smp[6 * N + i]);
+            } else {
+                p[u] = pin[i];
+                q[u] = qin[i];
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (j0 + u * kStatThreads >= b) break;
+            const int it = i0 + u;
+            if (first + it * 64 >= N) continue;
+            const int digit = min((kv[it] >> shift) & (kMaxBins - 1), bins - 1);
+            const int64_t dst = (int64_t)gbase[digit] + wc[w * bins + digit] + rank[it];
+            p[u].w = __int_as_float((int32_t)dst);
+            pout[dst] = p[u];
+            qout[dst] = q[u];
+            if (kout) kout[dst] = kv[it];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// A round's chunks: the leaves of a round are cut into chunks of at most kChunk records,
+// one work group each, so a few huge leaves fill the chip as well as many small ones (one
+// group per leaf took 640 us per round on 512 leaves of 1e4 to 2e5 samples). A leaf's
+// chunks are of one size (a multiple of 64), the last of what is left.
+// ---------------------------------------------------------------------------------
+__device__ __forceinline__ void chunk_range(const Entry& e, int32_t q, int32_t& lo, int32_t& hi)
+{
+    const int32_t cs = ((e.count + e.nch - 1) / e.nch + 63) & ~63;
+    lo = min(e.count, q * cs);
+    hi = min(e.count, lo + cs);
+}
+
+// a thread's running statistics
+struct Stat {
+    double s1[3] = {0, 0, 0}, sq[3] = {0, 0, 0};
+    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+    __device__ __forceinline__ void add(const float4& p)
+    {
+        const float v[3] = {p.x, p.y, p.z};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double x = (double)v[d];
+            s1[d] += x;
+            sq[d] += x * x;
+            mn[d] = fminf(mn[d], v[d]);
+            mx[d] = fmaxf(mx[d], v[d]);
+        }
+    }
+    __device__ __forceinline__ void merge(const Part& o)
+    {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            s1[d] += o.s1[d];
+            sq[d] += o.sq[d];
+            mn[d] = fminf(mn[d], o.mn[d]);
+            mx[d] = fmaxf(mx[d], o.mx[d]);
+        }
+    }
+    // over the wave, in a fixed order (every lane gets the result)
+    __device__ __forceinline__ void wave_reduce()
+    {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            s1[d] = wave_sum_f64(s1[d]);
+            sq[d] = wave_sum_f64(sq[d]);
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1)
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const float xf = xs[u][d];
-                const double x = (double)xf;
-                s1[d] += x;
-                sq[d] += x * x;
-                mn[d] = fminf(mn[d], xf);
-                mx[d] = fmaxf(mx[d], xf);
+                mn[d] = fminf(mn[d], __shfl_xor(mn[d], o));
+                mx[d] = fmaxf(mx[d], __shfl_xor(mx[d], o));
             }
-        }
     }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
+    __device__ __forceinline__ Part part() const
+    {
+        Part o;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            s1[d] += __shfl_xor(s1[d], o);
-            sq[d] += __shfl_xor(sq[d], o);
-            mn[d] = fminf(mn[d], __shfl_xor(mn[d], o));
-            mx[d] = fmaxf(mx[d], __shfl_xor(mx[d], o));
+            o.s1[d] = s1[d];
+            o.sq[d] = sq[d];
+            o.mn[d] = mn[d];
+            o.mx[d] = mx[d];
         }
+        return o;
     }
-    if (lane == 0)
-        for (int d = 0; d < 3; ++d) {
-            ls1[w][d] = s1[d];
-            lsq[w][d] = sq[d];
-            lmn[w][d] = mn[d];
-            lmx[w][d] = mx[d];
-        }
+};
+
+// the work group's statistics from its threads': waves by butterfly, then the waves in order
+__device__ __forceinline__ void block_part(Stat& s, Part* shared, Part* out)
+{
+    constexpr int W = kChunkThreads / 64;
+    s.wave_reduce();
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) shared[threadIdx.x >> 6] = s.part();
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int d = 0; d < 3; ++d) {  // the waves' results in wave order
-            s1[d] = ls1[0][d];
-            sq[d] = lsq[0][d];
-            mn[d] = lmn[0][d];
-            mx[d] = lmx[0][d];
-            for (int q = 1; q < W; ++q) {
-                s1[d] += ls1[q][d];
-                sq[d] += lsq[q][d];
-                mn[d] = fminf(mn[d], lmn[q][d]);
-                mx[d] = fmaxf(mx[d], lmx[q][d]);
+        Stat t;
+        for (int q = 0; q < W; ++q) t.merge(shared[q]);
+        *out = t.part();
+    }
+}
+
+// the records of a thread in a chunk: wave w holds the chunk's records [1024 w, 1024 (w + 1)),
+// lane l of step it record 1024 w + 64 it + l (a record past the end is the last one again)
+__device__ __forceinline__ void load_chunk(const float4* __restrict__ p, int32_t n, float4 (&r)[kChunkItems])
+{
+    const int first = (threadIdx.x >> 6) * (64 * kChunkItems) + (threadIdx.x & 63);
+#pragma unroll
+    for (int it = 0; it < kChunkItems; ++it)
+        if (first - (int)(threadIdx.x & 63) + it * 64 < n) r[it] = p[min(first + it * 64, n - 1)];
+}
+
+__global__ __launch_bounds__(kChunkThreads) void chunk_stats_kernel(const float4* __restrict__ P, RoundBufs rb,
+                                                                    const int32_t* __restrict__ ctl)
+{
+    __shared__ Part sh[kChunkThreads / 64];
+    const int32_t n_items = ctl[kCtlItems];
+    const int first = (threadIdx.x >> 6) * (64 * kChunkItems) + (threadIdx.x & 63);
+    for (int32_t k = blockIdx.x; k < n_items; k += gridDim.x) {
+        const Entry e = rb.entries[0][rb.items[0][k]];
+        int32_t lo, hi;
+        chunk_range(e, k - e.item0, lo, hi);
+        float4 r[kChunkItems];
+        load_chunk(P + e.start + lo, hi - lo, r);
+        Stat s;
+#pragma unroll
+        for (int it = 0; it < kChunkItems; ++it)
+            if (first + it * 64 < hi - lo) s.add(r[it]);
+        block_part(s, sh, &rb.parts[0][k]);
+    }
+}
+
+// goes right: the split of the tree's walk (FP32 coordinate against FP64 split)
+__device__ __forceinline__ bool goes_right(const float4& p, int ax, double split)
+{
+    const float v = ax == 0 ? p.x : (ax == 1 ? p.y : p.z);
+    return !((double)v < split);
+}
+
+// A round's first launch: every chunk's group sums its leaf's partial statistics (one wave,
+// fixed order; the other waves' records are on their way), which gives the split at the
+// mean of the axis of largest variance (lowest axis on ties), wanted only if samples fall
+// on both sides; and counts its records on the right.
+__global__ __launch_bounds__(kChunkThreads) void count_kernel(const float4* __restrict__ P0, const float4* __restrict__ P1,
+                                                              RoundBufs rb, int par, const int32_t* __restrict__ ctl)
+{
+    __shared__ int ax_s, want_s, right_s;
+    __shared__ double split_s;
+    const int32_t n_items = ctl[kCtlItems + par];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int first = w * (64 * kChunkItems) + lane;
+    for (int32_t k = blockIdx.x; k < n_items; k += gridDim.x) {
+        const int32_t ei = rb.items[par][k];
+        const Entry e = rb.entries[par][ei];
+        int32_t lo, hi;
+        chunk_range(e, k - e.item0, lo, hi);
+        const int32_t n = hi - lo;
+        float4 r[kChunkItems];
+        load_chunk((e.src ? P1 : P0) + e.start + lo, n, r);
+        __syncthreads();  // the previous item's shared words have been read
+        if (w == 0) {
+            Stat s;
+            const Part* parts = rb.parts[par] + (int64_t)(e.pn2 & 1) * rb.max_items + e.pfirst;
+            for (int32_t j = lane; j < (e.pn2 >> 1); j += 64) s.merge(parts[j]);
+            s.wave_reduce();
+            if (lane == 0) {
+                const double M = (double)e.count;
+                int ax = 0;
+                double best = -1.0;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const double mean = s.s1[d] / M;
+                    const double var = s.sq[d] / M - mean * mean;
+                    if (var > best) {
+                        best = var;
+                        ax = d;
+                    }
+                }
+                const double split = (ax == 0 ? s.s1[0] : (ax == 1 ? s.s1[1] : s.s1[2])) / M;
+                const float mn = ax == 0 ? s.mn[0] : (ax == 1 ? s.mn[1] : s.mn[2]);
+                const float mx = ax == 0 ? s.mx[0] : (ax == 1 ? s.mx[1] : s.mx[2]);
+                const int want = ((double)mn < split && split <= (double)mx) ? 1 : 0;
+                ax_s = ax;
+                split_s = split;
+                want_s = want;
+                right_s = 0;
+                if (k == e.item0) {
+                    rb.ax[ei] = ax;
+                    rb.split[ei] = split;
+                    rb.flags[ei] = want;
+                }
             }
         }
-        const double Md = (double)M;
-        int ax = 0;
-        double best = -1.0;
-        for (int d = 0; d < 3; ++d) {
-            const double mean = s1[d] / Md;
-            const double var = sq[d] / Md - mean * mean;
-            if (var > best) {
-                best = var;
-                ax = d;
-            }
+        __syncthreads();
+        const int ax = ax_s;
+        const double split = split_s;
+        int c = 0;
+#pragma unroll
+        for (int it = 0; it < kChunkItems; ++it)
+            c += __popcll(__ballot(first + it * 64 < n && goes_right(r[it], ax, split)));
+        if (lane == 0 && c) atomicAdd(&right_s, c);
+        __syncthreads();
+        if (threadIdx.x == 0 && want_s) {
+            rb.item_right[k] = right_s;
+            if (right_s) atomicAdd(&rb.rtot[par][ei], right_s);
         }
-        const double split = s1[ax] / Md;
-        want[l] = ((double)mn[ax] < split && split <= (double)mx[ax]) ? 1 : 0;
-        sax[l] = ax;
-        spos[l] = split;
+    }
+}
+
+// A round's last launch: the chunks of the leaves that split are partitioned, stably, from
+// one record buffer into the other (left samples from the segment's start, right ones
+// after all left ones); a child that may split in its turn gets its partial statistics
+// here, while the records are in registers.
+__global__ __launch_bounds__(kChunkThreads) void partition_kernel(float4* __restrict__ P0, float4* __restrict__ P1,
+                                                                  RoundBufs rb, int par,
+                                                                  const int32_t* __restrict__ ctl)
+{
+    __shared__ Part sh[kChunkThreads / 64];
+    __shared__ int32_t before_s, wr[kChunkThreads / 64];
+    const int32_t n_items = ctl[kCtlItems + par];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const int first = w * (64 * kChunkItems) + lane;
+    for (int32_t k = blockIdx.x; k < n_items; k += gridDim.x) {
+        const int32_t ei = rb.items[par][k];
+        const int fl = rb.flags[ei];
+        if (!(fl & 1)) continue;  // the same in every thread
+        const Entry e = rb.entries[par][ei];
+        const int ax = rb.ax[ei];
+        const double split = rb.split[ei];
+        const int32_t n_left = e.count - rb.rtot[par][ei];
+        int32_t lo, hi;
+        chunk_range(e, k - e.item0, lo, hi);
+        const int32_t n = hi - lo;
+        float4 r[kChunkItems];
+        load_chunk((e.src ? P1 : P0) + e.start + lo, n, r);
+        __syncthreads();  // the previous item's shared words have been read
+        if (w == 0) {  // the leaf's right samples in earlier chunks
+            int32_t b = 0;
+            for (int32_t j = e.item0 + lane; j < k; j += 64) b += rb.item_right[j];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) b += __shfl_xor(b, o);
+            if (lane == 0) before_s = b;
+        }
+        uint64_t m[kChunkItems];
+        int c = 0;
+#pragma unroll
+        for (int it = 0; it < kChunkItems; ++it) {
+            m[it] = __ballot(first + it * 64 < n && goes_right(r[it], ax, split));
+            c += __popcll(m[it]);
+        }
+        if (lane == 0) wr[w] = c;
+        __syncthreads();
+        int32_t rights = before_s;
+        for (int q = 0; q < w; ++q) rights += wr[q];
+        float4* out = (e.src ? P0 : P1) + e.start;
+#pragma unroll
+        for (int it = 0; it < kChunkItems; ++it) {
+            const int32_t at = first + it * 64;  // index in the chunk
+            const int32_t rb4 = rights + __popcll(m[it] & lt);
+            if (at < n) {
+                const bool right = (m[it] >> lane) & 1;
+                out[right ? n_left + rb4 : lo + at - rb4] = r[it];
+            }
+            rights += __popcll(m[it]);
+        }
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            if (!(fl & (2 << side))) continue;
+            Stat s;
+#pragma unroll
+            for (int it = 0; it < kChunkItems; ++it)
+                if (first + it * 64 < n && (int)((m[it] >> lane) & 1) == side) s.add(r[it]);
+            block_part(s, sh, &rb.parts[par ^ 1][(int64_t)side * rb.max_items + k]);
+        }
     }
 }
 
 // ---------------------------------------------------------------------------------
-// split decisions in leaf order by one work group; ctl[0] = splits made, ctl[1] |= 1
-// when the capacity stopped some
+// A round's decisions, by one work group, over the round's list (its leaves in increasing
+// order): the wanted splits are numbered by a block prefix sum, those beyond the node or
+// leaf capacity are skipped (status bit 1); the tree, the boxes and the leaf tables are
+// updated, and the next round's list takes the children with more than c samples, the left
+// ones (which keep their parents' indices) before the right ones, which is their order.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, int32_t L, const int32_t* __restrict__ want,
-                                                            const int32_t* __restrict__ sax,
-                                                            const double* __restrict__ spos,
-                                                            int32_t* __restrict__ act,
-                                                            int32_t* __restrict__ parent_of, int32_t* __restrict__ ctl)
+__global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, RoundBufs rb, int par, int32_t c, LeafTabs lt,
+                                                            int32_t* __restrict__ ctl)
 {
-    __shared__ int32_t part[1024];
+    __shared__ int64_t ws[16];
+    __shared__ int32_t ws32[16];
+    const int32_t n = ctl[kCtlEntries + par];
+    if (n == 0) {  // the same in every thread
+        if (threadIdx.x == 0) ctl[kCtlEntries + (par ^ 1)] = ctl[kCtlItems + (par ^ 1)] = 0;
+        return;
+    }
     const int32_t nodes = t.counts[0], leaves = t.counts[1];
-    const int32_t chunk = (L + 1023) / 1024;
-    const int32_t a = min(L, (int32_t)threadIdx.x * chunk), b = min(L, a + chunk);
-    int32_t s = 0;
-    for (int32_t l = a; l < b; ++l) s += want[l];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int32_t add = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
+    const int32_t cap = max(0, min((t.max_nodes - nodes) / 2, t.max_leaves - leaves));
+    int32_t total = 0;
+    int64_t lefts = 0;  // (entries << 32) + work items of the left children of the next list
+    for (int32_t e0 = 0; e0 < n; e0 += 1024) {
+        const int32_t ei = e0 + (int32_t)threadIdx.x;
+        const bool in = ei < n;
+        const int want = in ? rb.flags[ei] & 1 : 0;
+        int32_t all;
+        const int32_t rk = total + block_scan_1024(want, ws32, all);
+        total += all;
+        const bool go = want && rk < cap;
+        int64_t la = 0;
+        if (in) {
+            int fl = 0;
+            if (go) {
+                const Entry e = rb.entries[par][ei];
+                const int32_t nr = rb.rtot[par][ei], nl = e.count - nr;
+                fl = 1 | (nl > c ? 2 : 0) | (nr > c ? 4 : 0);
+                if (nl > c) la = (int64_t(1) << 32) | chunks_of(nl);
+                const int32_t l = e.leaf, r = leaves + rk, Ln = nodes + 2 * rk;
+                const int32_t nd = t.leaf_node[l];
+                const int ax = rb.ax[ei];
+                const double sp = rb.split[ei];
+                t.axis[nd] = ax;
+                t.split[nd] = sp;
+                t.left[nd] = Ln;
+                t.leaf[nd] = -1;
+                for (int q = 0; q < 2; ++q) {
+                    t.axis[Ln + q] = -1;
+                    t.left[Ln + q] = -1;
+                    t.split[Ln + q] = 0.0;
+                }
+                t.leaf[Ln] = l;
+                t.leaf[Ln + 1] = r;
+                t.leaf_node[l] = Ln;
+                t.leaf_node[r] = Ln + 1;
+                for (int d = 0; d < 3; ++d) {
+                    t.lo[3 * r + d] = t.lo[3 * l + d];
+                    t.hi[3 * r + d] = t.hi[3 * l + d];
+                }
+                t.hi[3 * l + ax] = sp;
+                t.lo[3 * r + ax] = sp;
+                t.init[r] = t.init[l];
+                lt.origin[r] = lt.origin[l];
+                lt.count[l] = nl;
+                lt.start[r] = e.start + nl;
+                lt.count[r] = nr;
+                lt.par[l] = lt.par[r] = e.src ^ 1;
+            }
+            rb.flags[ei] = fl;
+        }
+        int64_t la_all;
+        (void)block_scan_1024(la, ws, la_all);
+        lefts += la_all;
     }
-    const int32_t total = part[1023];
-    const int32_t cap = min((t.max_nodes - nodes) / 2, t.max_leaves - leaves);
-    const int32_t n_split = min(total, max(cap, 0));
-    int32_t rank = part[threadIdx.x] - s;
-    for (int32_t l = a; l < b; ++l) {
-        const bool go = want[l] && rank < n_split;
-        if (want[l]) ++rank;
-        if (!go) {
-            act[l] = 0;
-            continue;
+    // the next list: left children from 0, right ones after all left ones
+    int64_t lrun = 0, rrun = lefts;
+    int32_t first_rank = 0;
+    for (int32_t e0 = 0; e0 < n; e0 += 1024) {
+        const int32_t ei = e0 + (int32_t)threadIdx.x;
+        const int fl = ei < n ? rb.flags[ei] : 0;
+        Entry e{};
+        int32_t nr = 0;
+        if (fl) {
+            e = rb.entries[par][ei];
+            nr = rb.rtot[par][ei];
         }
-        const int32_t rk = rank - 1;
-        const int32_t r = leaves + rk, Ln = nodes + 2 * rk;
-        const int32_t n = t.leaf_node[l];
-        const int ax = sax[l];
-        const double sp = spos[l];
-        t.axis[n] = ax;
-        t.split[n] = sp;
-        t.left[n] = Ln;
-        t.leaf[n] = -1;
-        for (int q = 0; q < 2; ++q) {
-            t.axis[Ln + q] = -1;
-            t.left[Ln + q] = -1;
-            t.split[Ln + q] = 0.0;
+        const int32_t nl = e.count - nr;
+        int32_t go_all;
+        const int32_t rk = first_rank + block_scan_1024(fl & 1, ws32, go_all);
+        first_rank += go_all;
+        int64_t all;
+        const int64_t a = lrun + block_scan_1024((fl & 2) ? (int64_t(1) << 32) | chunks_of(nl) : int64_t(0), ws, all);
+        lrun += all;
+        const int64_t b = rrun + block_scan_1024((fl & 4) ? (int64_t(1) << 32) | chunks_of(nr) : int64_t(0), ws, all);
+        rrun += all;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            if (!(fl & (2 << side))) continue;
+            const int64_t at = side ? b : a;
+            const int32_t en = (int32_t)(at >> 32), it = (int32_t)at, cnt = side ? nr : nl;
+            const int32_t nch = chunks_of(cnt);
+            rb.entries[par ^ 1][en] = Entry{side ? leaves + rk : e.leaf, side ? e.start + nl : e.start, cnt, e.src ^ 1,
+                                            it, nch, e.item0, 2 * e.nch + side};
+            rb.rtot[par ^ 1][en] = 0;
+            for (int32_t q = 0; q < nch; ++q) rb.items[par ^ 1][it + q] = en;
         }
-        t.leaf[Ln] = l;
-        t.leaf[Ln + 1] = r;
-        t.leaf_node[l] = Ln;
-        t.leaf_node[r] = Ln + 1;
-        for (int d = 0; d < 3; ++d) {
-            t.lo[3 * r + d] = t.lo[3 * l + d];
-            t.hi[3 * r + d] = t.hi[3 * l + d];
-        }
-        t.hi[3 * l + ax] = sp;
-        t.lo[3 * r + ax] = sp;
-        t.init[r] = t.init[l];
-        parent_of[rk] = l;
-        act[l] = 1;
-        act[r] = 1;
     }
-    __syncthreads();
+    __syncthreads();  // every thread has read the counts
     if (threadIdx.x == 0) {
+        const int32_t n_split = min(total, cap);
         t.counts[0] = nodes + 2 * n_split;
         t.counts[1] = leaves + n_split;
-        ctl[0] = n_split;
-        ctl[1] |= total > n_split ? 1 : 0;
+        ctl[kCtlEntries + (par ^ 1)] = (int32_t)(rrun >> 32);
+        ctl[kCtlItems + (par ^ 1)] = (int32_t)rrun;
+        ctl[kCtlStatus] |= total > n_split ? 1 : 0;
+        ctl[kCtlLeaves] = leaves + n_split;
     }
 }
 
-// the new leaf r = leaves_before + rank copies its parent's mixture and state
-__global__ void copy_leaves_kernel(int32_t leaves_before, int32_t n_split, const int32_t* __restrict__ parent_of,
-                                   int K, MixPtrs mix, StatePtrs st)
+// After the last round (each kernel below leaves at once while a leaf is left to split):
+// off[l] = first output position of leaf l, off[L] = N, by one work group.
+__global__ __launch_bounds__(1024) void offsets_kernel(const int32_t* __restrict__ ctl, int done, LeafTabs lt,
+                                                       int64_t* __restrict__ off)
 {
-    const int rk = blockIdx.x;
-    if (rk >= n_split) return;
-    const int64_t r = leaves_before + rk, l = parent_of[rk];
-    for (int q = threadIdx.x; q < 38 * K + 2; q += blockDim.x) {
-        if (q < K) mix.pi[r * K + q] = mix.pi[l * K + q];
-        else if (q < 4 * K) mix.mud[r * 3 * K + q - K] = mix.mud[l * 3 * K + q - K];
-        else if (q < 7 * K) mix.mux[r * 3 * K + q - 4 * K] = mix.mux[l * 3 * K + q - 4 * K];
-        else if (q < 22 * K) mix.cov[r * 15 * K + q - 7 * K] = mix.cov[l * 15 * K + q - 7 * K];
-        else if (q < 23 * K) st.s0[r * K + q - 22 * K] = st.s0[l * K + q - 22 * K];
-        else if (q < 38 * K) st.s2[r * 15 * K + q - 23 * K] = st.s2[l * 15 * K + q - 23 * K];
-        else if (q == 38 * K) st.sw[r] = st.sw[l];
-        else st.step[r] = st.step[l];
+    __shared__ int64_t ws[16];
+    if (!finished(ctl, done)) return;
+    const int32_t L = ctl[kCtlLeaves];
+    int64_t run = 0;
+    for (int32_t l0 = 0; l0 < L; l0 += 1024) {
+        const int32_t l = l0 + (int32_t)threadIdx.x;
+        int64_t all;
+        const int64_t x = run + block_scan_1024<int64_t>(l < L ? lt.count[l] : 0, ws, all);
+        if (l < L) off[l] = x;
+        run += all;
+    }
+    if (threadIdx.x == 0) off[L] = run;
+}
+
+// a new leaf copies the mixture and state of the leaf it was split from
+__global__ void copy_leaves_kernel(int32_t L0, const int32_t* __restrict__ ctl, int done,
+                                   const int32_t* __restrict__ origin, int K, MixPtrs mix, StatePtrs st)
+{
+    if (!finished(ctl, done)) return;
+    const int32_t L = ctl[kCtlLeaves];
+    for (int64_t r = L0 + (int64_t)blockIdx.x; r < L; r += gridDim.x) {
+        const int64_t l = origin[r];
+        for (int q = threadIdx.x; q < 38 * K + 2; q += blockDim.x) {
+            if (q < K) mix.pi[r * K + q] = mix.pi[l * K + q];
+            else if (q < 4 * K) mix.mud[r * 3 * K + q - K] = mix.mud[l * 3 * K + q - K];
+            else if (q < 7 * K) mix.mux[r * 3 * K + q - 4 * K] = mix.mux[l * 3 * K + q - 4 * K];
+            else if (q < 22 * K) mix.cov[r * 15 * K + q - 7 * K] = mix.cov[l * 15 * K + q - 7 * K];
+            else if (q < 23 * K) st.s0[r * K + q - 22 * K] = st.s0[l * K + q - 22 * K];
+            else if (q < 38 * K) st.s2[r * 15 * K + q - 23 * K] = st.s2[l * 15 * K + q - 23 * K];
+            else if (q == 38 * K) st.sw[r] = st.sw[l];
+            else st.step[r] = st.step[l];
+        }
     }
 }
 
-__global__ void set_active_kernel(int32_t* __restrict__ act, const int32_t* __restrict__ counts, int32_t max_leaves,
-                                  int32_t* __restrict__ ctl)
+// largest l in [0, L) with off[l] <= j (off[0] = 0 <= j < off[L]), by a 64-ary search of
+// the wave
+__device__ __forceinline__ int32_t find_leaf(const int64_t* __restrict__ off, int32_t L, int64_t j)
 {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l < min(counts[1], max_leaves)) act[l] = 1;
-    if (l == 0) ctl[0] = ctl[1] = 0;
+    const int lane = threadIdx.x & 63;
+    int32_t a = 0, n = L;
+    while (n > 1) {
+        const int32_t step = (n + 63) / 64;
+        const int32_t idx = a + lane * step;
+        const uint64_t m = __ballot(idx < a + n && off[min(idx, a + n - 1)] <= j);
+        const int q = 63 - __builtin_clzll(m);  // lane 0's leaf starts at or before j
+        const int32_t end = a + n;
+        a += q * step;
+        n = min(step, end - a);
+    }
+    return a;
 }
 
-// Work groups go to the eight XCDs in turn (group b to XCD b % 8), each XCD with its own
-// L2. The groups of one XCD take consecutive ranges of the output, so that a source line
-// a run of gathered samples only partly covers is fetched into one L2, not into two.
-__device__ __forceinline__ int64_t xcd_block_order(int64_t b, int64_t nb)
+// The samples in the order of the leaf indices: a leaf's positions from its segment, its
+// directions and weights by the index that travelled with them, which lies in the segment
+// of the leaf it was split from (a window that stays in cache).
+constexpr int kGatherPer = 4;
+__global__ __launch_bounds__(256) void gather_kernel(const int32_t* __restrict__ ctl, int done, int64_t N, LeafTabs lt,
+                                                     const int64_t* __restrict__ off, const float4* __restrict__ P0,
+                                                     const float4* __restrict__ P1, const float4* __restrict__ Q,
+                                                     float* __restrict__ out)
 {
-    const int64_t x = b % 8, q = b / 8, per = nb / 8, extra = nb % 8;
-    return x * per + (x < extra ? x : extra) + q;
-}
-
-__global__ void gather_kernel(const float* __restrict__ smp, int64_t N, const int32_t* __restrict__ perm,
-                              float* __restrict__ out)
-{
-    const int64_t j = xcd_block_order(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    const int32_t i = perm[j];
+    if (!finished(ctl, done)) return;
+    const int32_t L = ctl[kCtlLeaves];
+    const int64_t wave = xcd_block_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t j0 = wave * (64 * kGatherPer);
+    if (j0 >= N) return;
+    const int64_t jl = min(j0 + 64 * kGatherPer, N) - 1;
+    const int32_t l0 = find_leaf(off, L, j0);
+    const int32_t l1 = off[l0 + 1] > jl ? l0 : find_leaf(off, L, jl);
+    float4 p[kGatherPer], q[kGatherPer];
 #pragma unroll
-    for (int a = 0; a < 7; ++a) out[a * N + j] = smp[a * N + i];
+    for (int u = 0; u < kGatherPer; ++u) {
+        const int64_t j = min(j0 + u * 64 + (threadIdx.x & 63), jl);
+        int32_t a = l0, b = l1;  // the lane's leaf in [a, b]
+        while (a < b) {
+            const int32_t mid = (a + b + 1) / 2;
+            if (off[mid] <= j) a = mid;
+            else b = mid - 1;
+        }
+        p[u] = (lt.par[a] ? P1 : P0)[lt.start[a] + (j - off[a])];
+    }
+#pragma unroll
+    for (int u = 0; u < kGatherPer; ++u) q[u] = Q[__float_as_int(p[u].w)];
+#pragma unroll
+    for (int u = 0; u < kGatherPer; ++u) {
+        const int64_t j = j0 + u * 64 + (threadIdx.x & 63);
+        if (j > jl) continue;
+        out[j] = q[u].x;
+        out[N + j] = q[u].y;
+        out[2 * N + j] = q[u].z;
+        out[3 * N + j] = p[u].x;
+        out[4 * N + j] = p[u].y;
+        out[5 * N + j] = p[u].z;
+        out[6 * N + j] = q[u].w;
+    }
 }
 
 // Initial mixture of an uninitialised leaf with at least min_init samples, one thread
@@ -808,11 +1092,8 @@ __global__ void gather_kernel(const float* __restrict__ smp, int64_t N, const in
 // centre -+ d/4; four: a 2x2 pattern; more: evenly), directional variance 2 pi / 8,
 // positional variance r^2 / chi2_3^-1(0.9) with r = 2 d / n_pos, weights 1/K; the
 // Robbins-Monro state starts at zero.
-__global__ void init_leaves_kernel(TreePtrs t, int32_t L, const int64_t* __restrict__ off, int32_t min_init, int K,
-                                   MixPtrs mix, StatePtrs st)
+__device__ __forceinline__ void init_leaf(const TreePtrs& t, int32_t l, int K, const MixPtrs& mix, const StatePtrs& st)
 {
-    const int l = blockIdx.x;
-    if (l >= L || t.init[l] || off[l + 1] - off[l] < min_init) return;
     const double chi2_3_inv_090 = 6.251388631170325;
     const int n_dir = K < 8 ? K : 8;
     const int n_pos = (K + n_dir - 1) / n_dir;
@@ -862,37 +1143,63 @@ __global__ void init_leaves_kernel(TreePtrs t, int32_t L, const int64_t* __restr
     }
 }
 
+__global__ void init_leaves_kernel(TreePtrs t, const int32_t* __restrict__ ctl, int done, const int64_t* __restrict__ off,
+                                   int32_t min_init, int K, MixPtrs mix, StatePtrs st)
+{
+    if (!finished(ctl, done)) return;
+    const int32_t L = ctl[kCtlLeaves];
+    for (int32_t l = blockIdx.x; l < L; l += gridDim.x)
+        if (!t.init[l] && off[l + 1] - off[l] >= min_init) init_leaf(t, l, K, mix, st);
+}
+
 // workspace of a refinement
 struct TreeLayout {
-    size_t nodeof, keys0, keys1, vals0, vals1, hist, tsum, off, act, want, sax, spos, parent, ctl, total;
-    int B;
+    size_t keys[2], p[2], q[2], hist, gsum, total_bins, start, count, par, origin, entries[2], items[2], rtot[2],
+        parts[2], item_right, flags, ax, split, ctl, total;
+    int tiles, groups;
+    int32_t max_items;
 };
 
 inline TreeLayout tree_layout(int64_t N, int32_t max_leaves)
 {
     TreeLayout L{};
     const int64_t n = N > 0 ? N : 1;
-    L.B = (int)((n + kSortTile - 1) / kSortTile);
+    const int64_t bins = std::min<int64_t>(max_leaves, kMaxBins);
+    const bool passes = max_leaves > kMaxBins;  // more than one sorting pass may run
+    L.tiles = (int)((n + kSortTile - 1) / kSortTile);
+    L.groups = (L.tiles + kScanRows - 1) / kScanRows;
+    // a round's leaves are disjoint and not empty; each has one partly filled chunk at most
+    const int64_t leaves = std::min<int64_t>(max_leaves, n);
+    L.max_items = (int32_t)(n / kChunk + leaves);
     size_t p = 0;
     auto take = [&](size_t bytes) {
         const size_t at = p;
         p = align256(p + bytes);
         return at;
     };
-    L.nodeof = take(n * 4);
-    L.keys0 = take(n * 4);
-    L.keys1 = take(n * 4);
-    L.vals0 = take(n * 4);
-    L.vals1 = take(n * 4);
-    L.hist = take((size_t)kRadix * L.B * 4);
-    L.tsum = take(((size_t)kRadix * L.B + kScanTile - 1) / kScanTile * 4);
-    L.off = take(((size_t)max_leaves + 1) * 8);
-    L.act = take((size_t)max_leaves * 4);
-    L.want = take((size_t)max_leaves * 4);
-    L.sax = take((size_t)max_leaves * 4);
-    L.spos = take((size_t)max_leaves * 8);
-    L.parent = take((size_t)max_leaves * 4);
-    L.ctl = take(4 * 4);
+    L.keys[0] = take(n * 4);
+    L.keys[1] = passes ? take(n * 4) : L.keys[0];
+    for (int b = 0; b < 2; ++b) L.p[b] = take(n * 16);
+    L.q[0] = take(n * 16);
+    L.q[1] = passes ? take(n * 16) : L.q[0];
+    L.hist = take((size_t)bins * L.tiles * 4);
+    L.gsum = take((size_t)bins * L.groups * 4);
+    L.total_bins = take((size_t)bins * 4);
+    L.start = take(((size_t)max_leaves + 1) * 4);
+    L.count = take((size_t)max_leaves * 4);
+    L.par = take((size_t)max_leaves * 4);
+    L.origin = take((size_t)max_leaves * 4);
+    for (int b = 0; b < 2; ++b) {
+        L.entries[b] = take((size_t)leaves * sizeof(Entry));
+        L.items[b] = take((size_t)L.max_items * 4);
+        L.rtot[b] = take((size_t)leaves * 4);
+        L.parts[b] = take((size_t)L.max_items * 2 * sizeof(Part));
+    }
+    L.item_right = take((size_t)L.max_items * 4);
+    L.flags = take((size_t)leaves * 4);
+    L.ax = take((size_t)leaves * 4);
+    L.split = take((size_t)leaves * 8);
+    L.ctl = take(kCtlWords * 4);
     L.total = p;
     return L;
 }
@@ -953,109 +1260,119 @@ extern "C" int sdmm_tree_refine(const sdmm_tree* tree, const float* samples, int
     if (workspace_bytes < TL.total) return SDMM_ENOWORKSPACE;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     char* ws = reinterpret_cast<char*>(workspace);
-    int32_t* nodeof = reinterpret_cast<int32_t*>(ws + TL.nodeof);
-    int32_t* k0 = reinterpret_cast<int32_t*>(ws + TL.keys0);
-    int32_t* k1 = reinterpret_cast<int32_t*>(ws + TL.keys1);
-    int32_t* v0 = reinterpret_cast<int32_t*>(ws + TL.vals0);
-    int32_t* v1 = reinterpret_cast<int32_t*>(ws + TL.vals1);
-    int32_t* hist = reinterpret_cast<int32_t*>(ws + TL.hist);
-    int32_t* tsum = reinterpret_cast<int32_t*>(ws + TL.tsum);
-    int64_t* off = reinterpret_cast<int64_t*>(ws + TL.off);
-    int32_t* act = reinterpret_cast<int32_t*>(ws + TL.act);
-    int32_t* want = reinterpret_cast<int32_t*>(ws + TL.want);
-    int32_t* sax = reinterpret_cast<int32_t*>(ws + TL.sax);
-    double* spos = reinterpret_cast<double*>(ws + TL.spos);
-    int32_t* parent = reinterpret_cast<int32_t*>(ws + TL.parent);
-    int32_t* ctl = reinterpret_cast<int32_t*>(ws + TL.ctl);
+    auto i32 = [&](size_t at) { return reinterpret_cast<int32_t*>(ws + at); };
+    auto f4 = [&](size_t at) { return reinterpret_cast<float4*>(ws + at); };
+    int32_t *hist = i32(TL.hist), *gsum = i32(TL.gsum), *bin_total = i32(TL.total_bins), *ctl = i32(TL.ctl);
+    float4 *P0 = f4(TL.p[0]), *P1 = f4(TL.p[1]);
+    const LeafTabs lt{i32(TL.start), i32(TL.count), i32(TL.par), i32(TL.origin)};
+    RoundBufs rb;
+    for (int b = 0; b < 2; ++b) {
+        rb.entries[b] = reinterpret_cast<Entry*>(ws + TL.entries[b]);
+        rb.items[b] = i32(TL.items[b]);
+        rb.rtot[b] = i32(TL.rtot[b]);
+        rb.parts[b] = reinterpret_cast<Part*>(ws + TL.parts[b]);
+    }
+    rb.item_right = i32(TL.item_right);
+    rb.flags = i32(TL.flags);
+    rb.ax = i32(TL.ax);
+    rb.split = reinterpret_cast<double*>(ws + TL.split);
+    rb.max_items = TL.max_items;
     const TreePtrs tp = tree_ptrs(tree);
     const MixPtrs mp{mix->weights, mix->mean_dir, mix->mean_pos, mix->cov};
     const StatePtrs sp{state->s0, state->s2, state->sw, state->step};
     const int K = mix->K;
     int rc;
 
-    // the words read back once per round land in pinned memory (a pageable destination
-    // would be staged by the runtime), one buffer per host thread, kept for its lifetime
+    // the words read back land in pinned memory (a pageable destination would be staged by
+    // the runtime), one buffer per host thread, kept for its lifetime
     thread_local int32_t* pinned = nullptr;
-    if (!pinned && (rc = check(hipHostMalloc((void**)&pinned, 4 * sizeof(int32_t), hipHostMallocPortable)))) {
+    if (!pinned && (rc = check(hipHostMalloc((void**)&pinned, kCtlWords * sizeof(int32_t), hipHostMallocPortable)))) {
         pinned = nullptr;
         return rc;
     }
-    int32_t* counts = pinned;
-    int32_t* c2 = pinned + 2;
-
-    // what needs no leaf count on the host is queued ahead of its readback, so that the GPU
-    // works while the host waits: the location of every sample from the root, the active
-    // flags (from the count on the device) and the first pass of the radix sort. Only the
-    // workspace is written before the tree's counts are checked.
-    const unsigned loc_groups = std::min<unsigned>(blocks_for(N, kLocTile), kLocMaxGroups);
-    {  // the full location of every sample from the root is timed
-        ScopedTimer tm(SDMM_TIMER_TREE, s);
-        locate_kernel<true><<<loc_groups, kLocThreads, 0, s>>>(tp, samples, N, nodeof, k0);
-    }
-    set_active_kernel<<<blocks_for(tree->max_leaves, 256), 256, 0, s>>>(act, tree->counts, tree->max_leaves, ctl);
-    // the first round's stable LSD radix sort from the sample order, 8 bits per pass
-    const int32_t *kin = k0, *vin = nullptr;
-    int32_t *kout = k1, *vout = v1;
-    auto sort_pass = [&](int p) {
-        radix_hist_kernel<<<TL.B, kSortThreads, 0, s>>>(kin, N, p * kRadixBits, hist, TL.B);
-        const int64_t nh = (int64_t)kRadix * TL.B;
-        const unsigned nt = (unsigned)((nh + kScanTile - 1) / kScanTile);
-        scan_tile_sums_kernel<<<nt, 256, 0, s>>>(hist, nh, tsum);
-        scan_sums_kernel<<<1, 1024, 0, s>>>(tsum, nt);
-        scan_apply_kernel<<<nt, 256, 0, s>>>(hist, nh, tsum);
-        radix_scatter_kernel<<<TL.B, kSortThreads, 0, s>>>(kin, vin, N, p * kRadixBits, hist, TL.B, kout, vout);
-        kin = kout;
-        vin = vout;
-        kout = (kout == k1) ? k0 : k1;
-        vout = (vout == v1) ? v0 : v1;
+    auto read_back = [&](const int32_t* from, int n) {
+        const int e = check(hipMemcpyAsync(pinned, from, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        return e ? e : check(hipStreamSynchronize(s));
     };
-    if (N > 0) sort_pass(0);
-    if ((rc = check(hipMemcpyAsync(counts, tree->counts, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s))))
-        return rc;
-    if ((rc = check(hipStreamSynchronize(s)))) return rc;
-    int32_t L = counts[1];
-    if (L < 1 || L > tree->max_leaves || counts[0] < 1 || counts[0] > tree->max_nodes) return SDMM_EINVAL;
-    {
+
+    // the location needs no leaf count on the host, so the GPU works on it while the host
+    // waits for the tree's counts. Only the workspace is written before they are checked.
+    {  // timed
+        ScopedTimer tm(SDMM_TIMER_TREE, s);
+        if (N > 0)
+            locate_kernel<<<std::min<unsigned>((unsigned)TL.tiles, kLocMaxGroups), kLocThreads, 0, s>>>(
+                tp, samples, N, i32(TL.keys[0]), hist, TL.tiles);
+    }
+    if ((rc = read_back(tree->counts, 2))) return rc;
+    const int32_t L0 = pinned[1];
+    if (L0 < 1 || L0 > tree->max_leaves || pinned[0] < 1 || pinned[0] > tree->max_nodes) return SDMM_EINVAL;
+
+    // the stable sort by leaf: one pass up to kMaxBins leaves, which leaves the leaf tables
+    // and the first round's list behind; more leaves take more passes
+    int passes = 1;
+    while (passes < 3 && (int64_t(1) << (passes * kDigitBits)) < L0) ++passes;
+    for (int p = 0; p < passes && N > 0; ++p) {
+        const int shift = p * kDigitBits;
+        const int bins = (int)std::min<int64_t>(kMaxBins, ((int64_t)L0 + (int64_t(1) << shift) - 1) >> shift);
         int bits = 1;
-        while ((int64_t(1) << bits) < L) ++bits;
-        const int passes = (bits + kRadixBits - 1) / kRadixBits;
-        for (int p = 1; p < passes && N > 0; ++p) sort_pass(p);
+        while ((1 << bits) < bins) ++bits;
+        const int32_t* kin = i32(TL.keys[p & 1]);
+        int32_t* kout = passes > 1 ? i32(TL.keys[(p & 1) ^ 1]) : nullptr;
+        const int to = (passes - 1 - p) & 1;  // the last pass ends in buffer 0
+        if (p > 0) tile_hist_kernel<<<TL.tiles, kSortThreads, 0, s>>>(kin, N, shift, bins, hist);
+        scan_group_kernel<<<dim3((bins + 255) / 256, TL.groups), 256, 0, s>>>(hist, TL.tiles, bins, gsum);
+        scan_bins_kernel<<<(bins + 63) / 64, 64, 0, s>>>(gsum, TL.groups, bins, bin_total);
+        base_kernel<<<1, 1024, 0, s>>>(bin_total, bins, passes == 1 ? 1 : 0, L0, split_threshold, lt, rb, ctl);
+        const size_t lds = (size_t)bins * (4 + 2 * kSortWaves);
+        if (p == 0)
+            scatter_kernel<true><<<TL.tiles, kSortThreads, lds, s>>>(samples, nullptr, nullptr, kin, N, shift, bins, bits,
+                                                                     hist, gsum, bin_total, f4(TL.p[to]), f4(TL.q[to]),
+                                                                     kout);
+        else
+            scatter_kernel<false><<<TL.tiles, kSortThreads, lds, s>>>(nullptr, f4(TL.p[to ^ 1]), f4(TL.q[to ^ 1]), kin, N,
+                                                                      shift, bins, bits, hist, gsum, bin_total,
+                                                                      f4(TL.p[to]), f4(TL.q[to]), kout);
+    }
+    if (passes > 1 || N == 0) {
+        if (N > 0)
+            starts_kernel<<<blocks_for(N, 256), 256, 0, s>>>(i32(TL.keys[passes & 1]), N, L0, lt.start);
+        else if ((rc = check(hipMemsetAsync(lt.start, 0, ((size_t)L0 + 1) * 4, s))))
+            return rc;
+        base_kernel<<<1, 1024, 0, s>>>(bin_total, 0, 1, L0, split_threshold, lt, rb, ctl);
     }
 
-    const int32_t* sorted_vals = v0;
-    int32_t L_old = L;  // the leaf count before the last round's splits
-    for (int round = 0;; ++round) {
-        if (round > 0 && N > 0) {
-            // locate from the nodes reached before, then a stable partition of the
-            // previous order (k0 holds the new leaves)
-            locate_kernel<false><<<loc_groups, kLocThreads, 0, s>>>(tp, samples, N, nodeof, k0);
-            int32_t* pout = (vin == v0) ? v1 : v0;
-            part_count_kernel<<<TL.B, kSortThreads, 0, s>>>(vin, k0, N, L_old, hist, TL.B);
-            scan_sums_kernel<<<1, 1024, 0, s>>>(hist, (int64_t)TL.B + 1);
-            part_scatter_kernel<<<TL.B, kSortThreads, 0, s>>>(vin, k0, N, L_old, hist, TL.B, k1, pout);
-            kin = k1;
-            vin = pout;
+    // rounds, queued in groups: as many as the mean leaf would take to come down to the
+    // threshold and three more for the uneven ones (a round with an empty list costs three
+    // small launches, a wait for the host about 20 us), then what is left in groups of four.
+    // The launches that end the refinement follow each group and leave at once while a leaf
+    // is left to split.
+    const int64_t bound = N / kChunk + std::min<int64_t>(tree->max_leaves, N / ((int64_t)split_threshold + 1));
+    const unsigned groups = (unsigned)std::min<int64_t>(std::max<int64_t>(bound, 1), 4096);
+    if (N > split_threshold) chunk_stats_kernel<<<groups, kChunkThreads, 0, s>>>(P0, rb, ctl);
+    int ahead = 3;
+    while (ahead < 12 && ((int64_t)split_threshold * L0 << (ahead - 3)) < N) ++ahead;
+    if (N <= split_threshold) ahead = 0;
+    for (int round = 0;;) {
+        for (const int end = std::min(kMaxRounds, round + ahead); round < end; ++round) {
+            const int par = round & 1;
+            count_kernel<<<groups, kChunkThreads, 0, s>>>(P0, P1, rb, par, ctl);
+            split_decide_kernel<<<1, 1024, 0, s>>>(tp, rb, par, split_threshold, lt, ctl);
+            partition_kernel<<<groups, kChunkThreads, 0, s>>>(P0, P1, rb, par, ctl);
         }
-        sorted_vals = N > 0 ? vin : v0;
-        segment_kernel<<<blocks_for(std::max<int64_t>(N, (int64_t)L + 1), 256), 256, 0, s>>>(kin, N, L, off);
-        if (round == kMaxRounds) break;
-        // statistics and decisions
-        split_stats_kernel<<<L, kStatThreads, 0, s>>>(samples, N, vin, off, L, split_threshold, act, want, sax, spos);
-        split_decide_kernel<<<1, 1024, 0, s>>>(tp, L, want, sax, spos, act, parent, ctl);
-        if ((rc = check(hipMemcpyAsync(c2, ctl, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s)))) return rc;
-        if ((rc = check(hipStreamSynchronize(s)))) return rc;
-        if (c2[0] == 0) break;
-        copy_leaves_kernel<<<c2[0], 64, 0, s>>>(L, c2[0], parent, K, mp, sp);
-        L_old = L;
-        L += c2[0];
+        const int done = round >= kMaxRounds ? 2 : round & 1;
+        offsets_kernel<<<1, 1024, 0, s>>>(ctl, done, lt, cell_offsets_out);
+        if (N > 0)
+            gather_kernel<<<blocks_for(N, 256 * kGatherPer), 256, 0, s>>>(ctl, done, N, lt, cell_offsets_out, P0, P1,
+                                                                          f4(TL.q[0]), sorted_out);
+        if (round > 0)
+            copy_leaves_kernel<<<std::min(tree->max_leaves, 2048), 64, 0, s>>>(L0, ctl, done, lt.origin, K, mp, sp);
+        init_leaves_kernel<<<std::min(tree->max_leaves, 4096), 64, 0, s>>>(tp, ctl, done, cell_offsets_out, min_init, K,
+                                                                           mp, sp);
+        if ((rc = read_back(ctl, kCtlWords))) return rc;
+        if (done == 2 || pinned[kCtlEntries + done] == 0) break;
+        ahead = 4;
     }
-    if (N > 0) gather_kernel<<<blocks_for(N, 256), 256, 0, s>>>(samples, N, sorted_vals, sorted_out);
-    if ((rc = check(hipMemcpyAsync(cell_offsets_out, off, ((size_t)L + 1) * 8, hipMemcpyDeviceToDevice, s))))
-        return rc;
-    init_leaves_kernel<<<L, 64, 0, s>>>(tp, L, off, min_init, K, mp, sp);
-    if ((rc = check(hipMemcpyAsync(c2, ctl, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s)))) return rc;
-    if ((rc = check(hipStreamSynchronize(s)))) return rc;
-    *n_leaves_out = L;
-    if (status_out) *status_out = c2[1];
+    *n_leaves_out = pinned[kCtlLeaves];
+    if (status_out) *status_out = pinned[kCtlStatus];
     return check(hipGetLastError());
 }

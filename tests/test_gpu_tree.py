@@ -222,6 +222,33 @@ def test_tree_capacity_constant_positions_and_empty_input(dev, orc):
     _assert_refine_equal(t_gpu, t_orc, g, o)
 
 
+@pytest.mark.parametrize("n,depth,c,max_leaves", [
+    (1, 0, 1, 4),              # one sample
+    (4097, 0, 4096, 4),        # one sorting tile and one sample, one split
+    (8192, 0, 700, 64),        # one leaf of exactly one full chunk
+    (8193, 0, 700, 64),        # two chunks
+    (200003, 0, 1500, 512),    # one leaf of 25 chunks: many rounds, more than are queued at first
+    (150001, 1, 1, 40),        # every leaf wants to split: the capacity ends it
+    (140000, 4, 60, 16384),    # 4096 leaves in one pass, then more than 4096: two passes
+])
+def test_refine_at_the_edges_of_tiles_chunks_and_passes(dev, orc, n, depth, c, max_leaves):
+    """Sizes about the sorting tile (4096), the chunk (8192) and the bins of one sorting pass
+    (4096), each refined with two batches of samples (the second one on the refined tree)."""
+    print("case: refine", n, depth, c, max_leaves, flush=True)
+    from paper_2111_13094_amd import sdmm
+    t_gpu, t_orc, g, o = _refine_both(dev, orc, _samples(n, 21), c, max_leaves, depth=depth, seed=22,
+                                      n_init=min(3, 8 ** depth))
+    _assert_refine_equal(t_gpu, t_orc, g, o)
+    if depth == 4:
+        assert t_orc.n_leaves > 4096
+    smp2 = _samples(n + 77, 23)
+    mix, st = o[3], o[4]
+    gm, gst = g[4], g[5]
+    srt_g, off_g, L, status_g = sdmm.tree_refine(t_gpu, dev.from_numpy(smp2).cuda(), c, gm, gst, K)
+    status_o, srt_o, off_o = orc.tree_refine(t_orc, smp2, c, K, mix, st)
+    _assert_refine_equal(t_gpu, t_orc, (srt_g, off_g, L, status_g, gm, gst), (srt_o, off_o, status_o, mix, st))
+
+
 def test_refine_then_fit_matches_the_oracle(dev, orc):
     """The pipeline of one rendering iteration: refine with the iteration's samples,
     initialise leaves, then one batched EM step on the leaves."""
