@@ -157,11 +157,12 @@ void launch_stepwise(const int64_t* off, const float* smp, int64_t N, const sdmm
                      const sdmm_em_state& st, const sdmm_fit_opts& opts, int32_t* status, const Layout& L, char* ws,
                      hipStream_t s);
 
-// E-step over the items in record slots [slot_lo, slot_hi), one wave per slot; with
-// check, one more work group writes the offsets-check control words (the setup kernel's
-// job when it runs)
+// E-step over the items in record slots [slot_lo, slot_hi), one wave per slot, or one work
+// group of waves_per_group waves per slot (the wide pass); with check, one more work group
+// writes the offsets-check control words (the setup kernel's job when it runs)
 void launch_estep(EstepFn est, const float* smp, int64_t N, const int64_t* off, int C, int K, const Layout& L,
-                  int64_t slot_lo, int64_t slot_hi, int PS, char* ws, hipStream_t s, bool check = false);
+                  int64_t slot_lo, int64_t slot_hi, int PS, char* ws, hipStream_t s, bool check = false,
+                  int waves_per_group = 0);
 
 // Host-side record of which workspace holds E-step mirrors of the current parameters of
 // which mixture arrays: a batched fit with SDMM_FLAG_CARRY_MIRRORS writes them in its

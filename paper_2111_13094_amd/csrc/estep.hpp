@@ -303,12 +303,21 @@ __device__ __forceinline__ void weight_pass(const float* __restrict__ wch, int64
     const int lane = threadIdx.x & 63;
     double sw = 0.0;
     uint32_t cnt = 0, ng = 0;
-    for (int64_t b = s0; b < s1; b += 64) {  // wave-uniform trip count
-        const int64_t i = b + lane;
-        const float w = i < s1 ? wch[i] : 0.0f;
-        sw += (double)w;
-        cnt += (uint32_t)__popcll(__ballot(w > 0.0f));
-        ng += (uint32_t)__popcll(__ballot(w < 0.0f));
+    constexpr int U = 4;  // loads in flight; added in order
+    for (int64_t b = s0; b < s1; b += 64 * U) {  // wave-uniform trip count
+        float w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = b + u * 64 + lane;
+            w[u] = wch[min(i, s1 - 1)];
+            if (i >= s1) w[u] = 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            sw += (double)w[u];
+            cnt += (uint32_t)__popcll(__ballot(w[u] > 0.0f));
+            ng += (uint32_t)__popcll(__ballot(w[u] < 0.0f));
+        }
     }
     W = wave_sum_f64(sw);
     M = (double)cnt;
@@ -387,6 +396,72 @@ __device__ __forceinline__ bool cell_items(const int64_t* off, int64_t N, int c,
     return true;
 }
 
+// One (sample, component) pair of an EM pass (not the adjoint), in three parts that the
+// one-wave and the wide pass share, so that both form the same values: the tangent
+// coordinates y and the log2 density l of the lane's component P (mirror floats 0-26, log2
+// constant c2, -inf past K); the lane's share e of the sample's density and its sum den
+// over the G component lanes; and the repair of a sample whose sum is tiny. The
+// responsibility is e / den.
+struct Pair {
+    float y[5], l, e, den;
+};
+
+template <int G, bool JAC>
+__device__ __forceinline__ Pair estep_pair(const float* P, float c2, const SampleRegs& cur)
+{
+    Pair q;
+    // tangent coordinates y = (log_mu w, p - mu_x); the 1e-18 offset on w'_x keeps
+    // the antipode away from 0/0 in the log map
+    const float xr = fmaf(P[0], cur.ox, fmaf(P[1], cur.oy, fmaf(P[2], cur.oz, 1e-18f)));
+    const float yr = fmaf(P[3], cur.ox, fmaf(P[4], cur.oy, P[5] * cur.oz));
+    const float zr = fmaf(P[6], cur.ox, fmaf(P[7], cur.oy, P[8] * cur.oz));
+    const float f = log_map_f32_offset(xr, yr, zr, q.y[0], q.y[1]);
+    q.y[2] = cur.px - P[9];
+    q.y[3] = cur.py - P[10];
+    q.y[4] = cur.pz - P[11];
+    // shifted log2 of pi_k N5(y; 0, Sigma_k) through the scaled inverse Cholesky factor
+    const float z0 = P[12] * q.y[0];
+    const float z1 = fmaf(P[13], q.y[0], P[14] * q.y[1]);
+    const float z2 = fmaf(P[15], q.y[0], fmaf(P[16], q.y[1], P[17] * q.y[2]));
+    const float z3 = fmaf(P[18], q.y[0], fmaf(P[19], q.y[1], fmaf(P[20], q.y[2], P[21] * q.y[3])));
+    const float z4 =
+        fmaf(P[22], q.y[0], fmaf(P[23], q.y[1], fmaf(P[24], q.y[2], fmaf(P[25], q.y[3], P[26] * q.y[4]))));
+    float l = fmaf(-z0, z0, c2);
+    l = fmaf(-z1, z1, l);
+    l = fmaf(-z2, z2, l);
+    l = fmaf(-z3, z3, l);
+    q.l = fmaf(-z4, z4, l);
+    if constexpr (JAC) {
+        q.l += __log2f(f);  // solid-angle density: times f (may be > 0)
+        q.e = __builtin_amdgcn_exp2f(q.l - group_max<G>(q.l));
+    } else {
+        // every l is at most -1 (the per-cell shift), so exp2(l) needs no maximum unless
+        // the sample's whole sum is tiny (pair_tiny)
+        q.e = __builtin_amdgcn_exp2f(q.l);
+    }
+    q.den = group_sum<G>(q.e);
+    return q;
+}
+
+// a sample far from every component, whose densities would lose precision or underflow
+template <bool JAC>
+__device__ __forceinline__ bool pair_tiny(const Pair& q)
+{
+    return !JAC && q.den < 0x1p-100f;
+}
+
+// the max-shifted form for the groups of a tiny sum; the others keep their values
+template <int G>
+__device__ __forceinline__ void repair_pair(Pair& q)
+{
+    const float m = group_max_negative<G>(q.l);
+    const float e2 = __builtin_amdgcn_exp2f(q.l - m);
+    const float den2 = group_sum<G>(e2);
+    const bool redo = q.den < 0x1p-100f;
+    q.e = redo ? e2 : q.e;
+    q.den = redo ? den2 : q.den;
+}
+
 // E-step of one segment [s0, s1) of a cell by one wave. mirror_cell points at the cell's
 // K FP32 mirrors. Writes the segment record part[] (RecordT, from the FP64 totals) from
 // lanes < G.
@@ -429,30 +504,32 @@ __device__ __forceinline__ void estep_segment(const float* __restrict__ smp, int
     // one (sample, component) pair per lane
     auto body = [&](const SampleRegs& cur, bool valid) {
         const float w = valid ? cur.w : 0.0f;
-
-        // tangent coordinates y = (log_mu w, p - mu_x); the 1e-18 offset on w'_x keeps
-        // the antipode away from 0/0 in the log map
-        float xr = fmaf(P[0], cur.ox, fmaf(P[1], cur.oy, fmaf(P[2], cur.oz, 1e-18f)));
-        float yr = fmaf(P[3], cur.ox, fmaf(P[4], cur.oy, P[5] * cur.oz));
-        float zr = fmaf(P[6], cur.ox, fmaf(P[7], cur.oy, P[8] * cur.oz));
-        if constexpr (ADJ) {  // add the residue of the FP32-rounded frame
+        float y0, y1, y2, y3, y4, resp;
+        // the adjoint's own values (see below)
+        float xr = 0.0f, yr = 0.0f, zr = 0.0f, f = 0.0f, z0 = 0.0f, z1 = 0.0f, z2 = 0.0f, z3 = 0.0f, z4 = 0.0f;
+        float lmax = 0.0f, den = 0.0f;
+        if constexpr (!ADJ) {
+            Pair q = estep_pair<G, JAC>(P, c2, cur);
+            if (__ballot(pair_tiny<JAC>(q))) repair_pair<G>(q);
+            resp = q.e * __builtin_amdgcn_rcpf(q.den);
+            y0 = q.y[0];
+            y1 = q.y[1];
+            y2 = q.y[2];
+            y3 = q.y[3];
+            y4 = q.y[4];
+        } else {
+            // as estep_pair, with the residues of the FP32-rounded frame and means added and
+            // the quadratic form in FP64 from the hi/lo factor and constant
+            xr = fmaf(P[0], cur.ox, fmaf(P[1], cur.oy, fmaf(P[2], cur.oz, 1e-18f)));
+            yr = fmaf(P[3], cur.ox, fmaf(P[4], cur.oy, P[5] * cur.oz));
+            zr = fmaf(P[6], cur.ox, fmaf(P[7], cur.oy, P[8] * cur.oz));
             xr += fmaf(P[32], cur.ox, fmaf(P[33], cur.oy, P[34] * cur.oz));
             yr += fmaf(P[35], cur.ox, fmaf(P[36], cur.oy, P[37] * cur.oz));
             zr += fmaf(P[38], cur.ox, fmaf(P[39], cur.oy, P[40] * cur.oz));
-        }
-        float y0, y1;
-        const float f = log_map_f32_offset(xr, yr, zr, y0, y1);
-        float y2 = cur.px - P[9], y3 = cur.py - P[10], y4 = cur.pz - P[11];
-        if constexpr (ADJ) {
-            y2 -= P[41];
-            y3 -= P[42];
-            y4 -= P[43];
-        }
-
-        // shifted log2 of pi_k N5(y; 0, Sigma_k) through the scaled inverse Cholesky factor
-        float z0, z1, z2, z3, z4, l;
-        double ld = 0.0;
-        if constexpr (ADJ) {  // FP64 quadratic form from the hi/lo factor and constant
+            f = log_map_f32_offset(xr, yr, zr, y0, y1);
+            y2 = cur.px - P[9] - P[41];
+            y3 = cur.py - P[10] - P[42];
+            y4 = cur.pz - P[11] - P[43];
             auto Lq = [&](int q) { return (double)P[12 + q] + (double)P[44 + q]; };
             const double e0 = y0, e1 = y1, e2 = y2, e3 = y3, e4 = y4;
             const double w0 = Lq(0) * e0;
@@ -461,59 +538,26 @@ __device__ __forceinline__ void estep_segment(const float* __restrict__ smp, int
             const double w3 = fma(Lq(6), e0, fma(Lq(7), e1, fma(Lq(8), e2, Lq(9) * e3)));
             const double w4 = fma(Lq(10), e0, fma(Lq(11), e1, fma(Lq(12), e2, fma(Lq(13), e3, Lq(14) * e4))));
             const double c2d = comp < K ? (double)P[27] + (double)P[59] : -INFINITY;
-            ld = c2d - w0 * w0 - w1 * w1 - w2 * w2 - w3 * w3 - w4 * w4;
+            const double ld = c2d - w0 * w0 - w1 * w1 - w2 * w2 - w3 * w3 - w4 * w4;
             z0 = (float)w0;
             z1 = (float)w1;
             z2 = (float)w2;
             z3 = (float)w3;
             z4 = (float)w4;
-            l = (float)ld;
-        } else {
-            z0 = P[12] * y0;
-            z1 = fmaf(P[13], y0, P[14] * y1);
-            z2 = fmaf(P[15], y0, fmaf(P[16], y1, P[17] * y2));
-            z3 = fmaf(P[18], y0, fmaf(P[19], y1, fmaf(P[20], y2, P[21] * y3)));
-            z4 = fmaf(P[22], y0, fmaf(P[23], y1, fmaf(P[24], y2, fmaf(P[25], y3, P[26] * y4))));
-            l = fmaf(-z0, z0, c2);
-            l = fmaf(-z1, z1, l);
-            l = fmaf(-z2, z2, l);
-            l = fmaf(-z3, z3, l);
-            l = fmaf(-z4, z4, l);
-        }
-        if constexpr (JAC) l += __log2f(f);  // solid-angle density: times f (may be > 0)
-
-        // responsibilities: log-sum-exp across the component lanes of this sample
-        float lmax = 0.0f, e, den;
-        if constexpr (JAC || ADJ) {
-            if constexpr (JAC) lmax = group_max<G>(l);
-            else lmax = group_max_negative<G>(l);
-            if constexpr (ADJ) e = __builtin_amdgcn_exp2f((float)(ld - (double)lmax));
-            else e = __builtin_amdgcn_exp2f(l - lmax);
+            lmax = group_max_negative<G>((float)ld);
+            const float e = __builtin_amdgcn_exp2f((float)(ld - (double)lmax));
             den = group_sum<G>(e);
-        } else {
-            // every l is at most -1 (the per-cell shift), so exp2(l) needs no maximum unless
-            // the sample's whole sum is tiny; such a group (rare: far from every component)
-            // takes the max-shifted form, the others keep their values
-            e = __builtin_amdgcn_exp2f(l);
-            den = group_sum<G>(e);
-            if (__ballot(den < 0x1p-100f)) {
-                const float m = group_max_negative<G>(l);
-                const float e2 = __builtin_amdgcn_exp2f(l - m);
-                const float den2 = group_sum<G>(e2);
-                const bool redo = den < 0x1p-100f;
-                e = redo ? e2 : e;
-                den = redo ? den2 : den;
-            }
+            resp = e * __builtin_amdgcn_rcpf(den);
         }
-        const float wr = w * (e * __builtin_amdgcn_rcpf(den));
+        const float wr = w * resp;
 
         const float t0 = wr * y0, t1 = wr * y1, t2 = wr * y2, t3 = wr * y3, t4 = wr * y4;
-        acc[0].add(wr);
-        acc[1].add(t0);
-        acc[2].add(t1);
-        acc[3].add(t2);
-        acc[4].add(t3);
-        acc[5].add(t4);
+        acc[0].fma_add(w, resp);
+        acc[1].fma_add(wr, y0);
+        acc[2].fma_add(wr, y1);
+        acc[3].fma_add(wr, y2);
+        acc[4].fma_add(wr, y3);
+        acc[5].fma_add(wr, y4);
         acc[6].fma_add(t0, y0);
         acc[7].fma_add(t1, y0);
         acc[8].fma_add(t1, y1);
@@ -615,6 +659,186 @@ __device__ __forceinline__ void estep_segment(const float* __restrict__ smp, int
 #pragma unroll
             for (int s = NS; s < NR; ++s) part[NS * G + (s - NS)] = (RT)v[s];
         }
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// The wide E-step: one item by a work group of NW waves, for launches with too few items
+// to fill the chip. A wave alone on its SIMD takes an item's 64 steps one after the other,
+// and the launch lasts that chain. Here the steps' pairs, which do not depend on each
+// other, are formed by the waves in turn (step i by wave i % NW) and left in LDS
+// (responsibility, coordinates, weight), kWideSteps steps at a time; then every wave adds
+// up its share of the 21 statistics over these steps, in step order. The values and every
+// sum's order are those of the one-wave pass: the record is bit for bit the same. One
+// 256-sample item at G = 16 takes 8.2 us instead of 16.9; with the chip full it takes 2.3
+// times as long as the one-wave pass (the LDS traffic of the pairs, 35 values a step), so
+// only small launches take it (kWideSlots).
+// ---------------------------------------------------------------------------------
+constexpr int kWideWaves = 8;
+constexpr int kWideSteps = 32;       // steps per chunk (2 KB of LDS each)
+
+// wave that adds up statistic s (0: S0, 1-5: S1, 6-20: S2 packed): the sums share the LDS
+// reads, which bound this part, so each wave's statistics name as few of the eight values
+// of a pair as may be (27 reads a step in all); the last wave also takes the weights
+__device__ constexpr int wide_owner(int s)
+{
+    constexpr int own[21] = {0, 0, 1, 2, 3, 4, 0, 1, 1, 2, 5, 2, 3, 5, 5, 3, 4, 6, 6, 7, 4};
+    return own[s];
+}
+
+// the row d of statistic s: S1[d], or S2[d, e] with e = wide_col(s)
+__device__ constexpr int wide_row(int s)
+{
+    if (s < 6) return s - 1;
+    int d = 0;
+    while (tri(d, d) < s - 6) ++d;
+    return d;
+}
+__device__ constexpr int wide_col(int s) { return s - 6 - tri(wide_row(s), 0); }
+
+// a pair's values in LDS, each of the 64 lanes' in a row: y, then the responsibility, the
+// weight and their product
+constexpr int kWideR = 5, kWideW = 6, kWideWr = 7, kWideVals = 8;
+typedef float WidePair[kWideVals][64];
+
+template <int ACC, int W>
+__device__ __forceinline__ void wide_accumulate(RunSum<ACC> (&acc)[kStats], const WidePair* pairs, int n, uint32_t done,
+                                                uint32_t full)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll 8
+    for (int i = 0; i < n; ++i) {
+        const WidePair& q = pairs[i];
+#pragma unroll
+        for (int s = 0; s < kStats; ++s) {
+            if (wide_owner(s) != W) continue;
+            if (s == 0) acc[s].fma_add(q[kWideW][lane], q[kWideR][lane]);
+            else if (s < 6) acc[s].fma_add(q[kWideWr][lane], q[wide_row(s)][lane]);
+            else acc[s].fma_add(q[kWideWr][lane] * q[wide_row(s)][lane], q[wide_col(s)][lane]);
+        }
+        // the one-wave pass folds its block sums after every kFoldEvery steps of its loop
+        // over full steps
+        if (ACC != kAccPlain && (done + i + 1) % kFoldEvery == 0 && done + i + 1 < full) {
+#pragma unroll
+            for (int s = 0; s < kStats; ++s)
+                if (wide_owner(s) == W) acc[s].fold();
+        }
+    }
+}
+
+template <int G, int ACC, int W>
+__device__ __forceinline__ void wide_finish(RunSum<ACC> (&acc)[kStats], RecordT<ACC, false>* __restrict__ part)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int s = 0; s < kStats; ++s) {
+        if (wide_owner(s) != W) continue;
+        double v = acc[s].total();
+        // over the sample slots, in the one-wave pass's order
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1) v += __shfl_xor(v, o);
+        if (lane < G) part[s * G + lane] = (RecordT<ACC, false>)v;
+    }
+}
+
+template <int G, int ACC, bool JAC, int NW>
+__device__ __forceinline__ void estep_segment_wide(const float* __restrict__ smp, int64_t N, int64_t s0, int64_t s1,
+                                                   const float* __restrict__ mirror_cell, int K,
+                                                   RecordT<ACC, false>* __restrict__ part)
+{
+    static_assert(NW == 8 && kWideSteps % NW == 0, "wide_owner names eight waves");
+    constexpr int S = 64 / G, PER = kWideSteps / NW;  // steps per wave and chunk
+    __shared__ WidePair pairs[kWideSteps];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int comp = lane % G, slot = lane / G;
+    const int kk = comp < K ? comp : K - 1;
+    const float4* mp = reinterpret_cast<const float4*>(mirror_cell + (int64_t)kk * kMirror);
+    float P[28];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+        const float4 v = mp[q];
+        P[4 * q] = v.x;
+        P[4 * q + 1] = v.y;
+        P[4 * q + 2] = v.z;
+        P[4 * q + 3] = v.w;
+    }
+    const float c2 = comp < K ? P[27] : -INFINITY;
+    const float* ch[7];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) ch[a] = smp + (int64_t)a * N + s0;
+    const uint32_t n = (uint32_t)(s1 - s0), last = n > 0 ? n - 1 : 0;
+    const uint32_t full = n / S, steps = (n + S - 1) / S;  // uniform over the group
+    RunSum<ACC> acc[kStats];
+    // the samples of the wave's steps of a chunk (a slot past the end loads the last sample)
+    SampleRegs cur[PER] = {};
+    auto fetch = [&](uint32_t base) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const uint32_t it = base + p * NW + wave;
+            if (it < steps) cur[p] = load_sample(ch, min(it * S + slot, last));
+        }
+    };
+    fetch(0);
+    for (uint32_t base = 0; base < steps; base += kWideSteps) {
+        // all of the wave's pairs of the chunk side by side (those past the end come from
+        // samples of an earlier chunk and are not stored)
+        Pair q[PER];
+        bool tiny = false;
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            q[p] = estep_pair<G, JAC>(P, c2, cur[p]);
+            tiny |= pair_tiny<JAC>(q[p]);
+        }
+        if (__ballot(tiny)) {
+#pragma unroll
+            for (int p = 0; p < PER; ++p) repair_pair<G>(q[p]);
+        }
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const uint32_t it = base + p * NW + wave;
+            if (it >= steps) continue;
+            const float w = it * S + slot <= last ? cur[p].w : 0.0f;
+            const float r = q[p].e * __builtin_amdgcn_rcpf(q[p].den);
+            WidePair& o = pairs[it - base];
+#pragma unroll
+            for (int d = 0; d < 5; ++d) o[d][lane] = q[p].y[d];
+            o[kWideR][lane] = r;
+            o[kWideW][lane] = w;
+            o[kWideWr][lane] = w * r;
+        }
+        if (base + kWideSteps < steps) fetch(base + kWideSteps);
+        __syncthreads();
+        const int cnt = (int)min((uint32_t)kWideSteps, steps - base);
+        switch (wave) {
+            case 0: wide_accumulate<ACC, 0>(acc, pairs, cnt, base, full); break;
+            case 1: wide_accumulate<ACC, 1>(acc, pairs, cnt, base, full); break;
+            case 2: wide_accumulate<ACC, 2>(acc, pairs, cnt, base, full); break;
+            case 3: wide_accumulate<ACC, 3>(acc, pairs, cnt, base, full); break;
+            case 4: wide_accumulate<ACC, 4>(acc, pairs, cnt, base, full); break;
+            case 5: wide_accumulate<ACC, 5>(acc, pairs, cnt, base, full); break;
+            case 6: wide_accumulate<ACC, 6>(acc, pairs, cnt, base, full); break;
+            default: wide_accumulate<ACC, 7>(acc, pairs, cnt, base, full); break;
+        }
+        __syncthreads();  // before the next chunk overwrites the pairs
+    }
+    switch (wave) {
+        case 0: wide_finish<G, ACC, 0>(acc, part); break;
+        case 1: wide_finish<G, ACC, 1>(acc, part); break;
+        case 2: wide_finish<G, ACC, 2>(acc, part); break;
+        case 3: wide_finish<G, ACC, 3>(acc, part); break;
+        case 4: wide_finish<G, ACC, 4>(acc, part); break;
+        case 5: wide_finish<G, ACC, 5>(acc, part); break;
+        case 6: wide_finish<G, ACC, 6>(acc, part); break;
+        default:
+            wide_finish<G, ACC, 7>(acc, part);
+            double W, M, neg;
+            weight_pass(smp + 6 * N, s0, s1, W, M, neg);
+            if (lane == 0) {
+                part[kStats * G] = (RecordT<ACC, false>)W;
+                part[kStats * G + 1] = (RecordT<ACC, false>)M;
+                part[kStats * G + 2] = (RecordT<ACC, false>)neg;
+            }
+            break;
     }
 }
 

@@ -206,6 +206,12 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t group, int wpb, int wave, in
 // ---------------------------------------------------------------------------------
 // E-step: one wave per work item (see wave_item), slots by the XCD-aware map
 // ---------------------------------------------------------------------------------
+// Most record slots of a launch that the wide E-step takes. Per iteration of one cell (E-step
+// and M-step, us, one-wave / wide pass): 64 items 27.9 / 20.1, 256 items 33.4 / 27.7, 512
+// 33.9 / 32.3, 1024 38.5 / 40.0 with 16 components; 256 items 57.3 / 46.9, 512 58.8 / 59.7
+// with 32; 256 25.3 / 22.9, 512 25.8 / 26.0 with 8.
+constexpr int64_t kWideSlots = 512;
+
 // waves per SIMD the E-step needs: the plain-sum EM pass fits five (96 registers), which
 // hides more of each item's start-up latency (cell search, mirror and first loads)
 template <int ACC, bool JAC, bool ADJ>
@@ -233,6 +239,27 @@ __global__ __launch_bounds__(256, (estep_min_waves<ACC, JAC, ADJ>())) void estep
     if (w < 0 || !wave_item(w, off, N, C, ps, slot_lo, slot_hi, c, t, s0, s1, n_items)) return;
     estep_segment<G, ACC, JAC, ADJ>(smp, N, s0, s1, mirror + (int64_t)c * K * kMirror, K,
                                     static_cast<RecordT<ACC, ADJ>*>(records) + t * PS);
+}
+
+// The wide E-step: one work group of NW waves per work item (see estep_segment_wide)
+template <int G, int ACC, bool JAC, int NW>
+__global__ __launch_bounds__(64 * NW) void estep_wide_kernel(const float* __restrict__ smp, int64_t N,
+                                                             const int64_t* __restrict__ off, int C, int ps,
+                                                             int64_t slot_lo, int64_t slot_hi,
+                                                             const float* __restrict__ mirror, int K, int PS,
+                                                             void* __restrict__ records, int32_t* __restrict__ control,
+                                                             int check_tree_max)
+{
+    if (check_tree_max >= 0 && blockIdx.x == gridDim.x - 1) {
+        offsets_check_block(off, N, C, ps, control, check_tree_max);
+        return;
+    }
+    const int64_t w = xcd_slot(blockIdx.x, 1, 0, slot_hi - slot_lo);
+    int c;
+    int64_t t, s0, s1, n_items;
+    if (w < 0 || !wave_item(w, off, N, C, ps, slot_lo, slot_hi, c, t, s0, s1, n_items)) return;  // the whole group
+    estep_segment_wide<G, ACC, JAC, NW>(smp, N, s0, s1, mirror + (int64_t)c * K * kMirror, K,
+                                        static_cast<RecordT<ACC, false>*>(records) + t * PS);
 }
 
 // FP64 adjoint pass (verification mode), same work map as estep_kernel
@@ -600,6 +627,31 @@ __global__ __launch_bounds__(256) void fused_kernel(const float* __restrict__ sm
 // ---------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------
+template <int G>
+static EstepFn estep_wide_for_g(int acc, bool jac)
+{
+    if (jac) {
+        if (acc == kAccPlain) return estep_wide_kernel<G, kAccPlain, true, kWideWaves>;
+        if (acc == kAccFp64) return estep_wide_kernel<G, kAccFp64, true, kWideWaves>;
+        return estep_wide_kernel<G, kAccTwoSum, true, kWideWaves>;
+    }
+    if (acc == kAccPlain) return estep_wide_kernel<G, kAccPlain, false, kWideWaves>;
+    if (acc == kAccFp64) return estep_wide_kernel<G, kAccFp64, false, kWideWaves>;
+    return estep_wide_kernel<G, kAccTwoSum, false, kWideWaves>;
+}
+
+static EstepFn estep_wide_function(int G, int acc, bool jac)
+{
+    switch (G) {
+        case 4: return estep_wide_for_g<4>(acc, jac);
+        case 8: return estep_wide_for_g<8>(acc, jac);
+        case 16: return estep_wide_for_g<16>(acc, jac);
+        case 32: return estep_wide_for_g<32>(acc, jac);
+        case 64: return estep_wide_for_g<64>(acc, jac);
+    }
+    return nullptr;
+}
+
 template <int G, bool ADJ>
 static EstepFn estep_for_g(int acc, bool jac)
 {
@@ -747,7 +799,7 @@ void launch_setup(const int64_t* off, int64_t N, const sdmm_mixtures& mix, int32
 }
 
 void launch_estep(EstepFn est, const float* smp, int64_t N, const int64_t* off, int C, int K, const Layout& L,
-                  int64_t slot_lo, int64_t slot_hi, int PS, char* ws, hipStream_t s, bool check)
+                  int64_t slot_lo, int64_t slot_hi, int PS, char* ws, hipStream_t s, bool check, int waves_per_group)
 {
     const int64_t waves = slot_hi - slot_lo;
     if (waves <= 0 && !check) return;
@@ -755,8 +807,10 @@ void launch_estep(EstepFn est, const float* smp, int64_t N, const int64_t* off, 
     // its XCD's groups; with the offsets check, one more work group (past every work item)
     // runs it
     const int64_t per = xcd_chunk(std::max<int64_t>(waves, 0));
-    const unsigned blocks = (unsigned)(kXcds * ((per + L.wpb - 1) / L.wpb)) + (check ? 1u : 0u);
-    hipLaunchKernelGGL(est, dim3(blocks), dim3(64 * L.wpb), 0, s, smp, N, off, C, L.ps, slot_lo, slot_hi,
+    const int wpb = waves_per_group > 0 ? 1 : L.wpb;  // items per group
+    const unsigned blocks = (unsigned)(kXcds * ((per + wpb - 1) / wpb)) + (check ? 1u : 0u);
+    hipLaunchKernelGGL(est, dim3(blocks), dim3(64 * (waves_per_group > 0 ? waves_per_group : L.wpb)), 0, s, smp, N, off,
+                       C, L.ps, slot_lo, slot_hi,
                        reinterpret_cast<const float*>(ws + L.mirror), K, PS, static_cast<void*>(ws + L.records),
                        reinterpret_cast<int32_t*>(ws + L.global_ok),
                        check ? tree_levels_launched(N, L.P, L.max_cell) : -1);
@@ -834,7 +888,15 @@ static int enqueue_fit(const FitArgs& a, hipStream_t s, const std::vector<int64_
     // stays zero, and the compensated pass is bit for bit the plain one, which needs fewer
     // registers
     const bool one_block = (L.P / (64 / G)) <= kFoldEvery;
-    EstepFn est = estep_function(G, (acc == kAccTwoSum && one_block) ? kAccPlain : acc, jac, false);
+    const int acc_run = (acc == kAccTwoSum && one_block) ? kAccPlain : acc;
+    EstepFn est = estep_function(G, acc_run, jac, false);
+    EstepFn est_wide = estep_wide_function(G, acc_run, jac);
+    // the E-step over record slots [lo, hi), by the wide pass where they are few
+    auto estep = [&](int64_t lo, int64_t hi, bool check) {
+        const bool wide = hi - lo <= kWideSlots;
+        launch_estep(wide ? est_wide : est, a.smp, a.N, a.off, C, K, L, lo, hi, L.ps_fit, a.ws, s, check,
+                     wide ? kWideWaves : 0);
+    };
     FusedFn fused = fused_function(G, acc, jac);
     const bool rec32 = acc != kAccFp64;  // record element type of these passes (RecordT)
     MstepFn mstep = mstep_function(G, rec32), mstep_packed = mstep_packed_function(G, rec32);
@@ -849,7 +911,7 @@ static int enqueue_fit(const FitArgs& a, hipStream_t s, const std::vector<int64_
     auto second_pass = [&](int64_t lo, int64_t hi, int cell, int64_t c0, int64_t c1) {
         {
             ScopedTimer tm(SDMM_TIMER_ACCURATE, s);
-            launch_estep(est, a.smp, a.N, a.off, C, K, L, lo, hi, L.ps_fit, a.ws, s);
+            estep(lo, hi, false);
         }
         launch_tree(kTreeFit, a.off, a.N, C, K, L, cell, c0, c1, a.ws, s, rec32);
     };
@@ -875,7 +937,7 @@ static int enqueue_fit(const FitArgs& a, hipStream_t s, const std::vector<int64_
                     c1 = (*host_off)[c + 1];
                     first = c + (c0 >> L.ps);
                     n_items = c1 > c0 ? (c1 - c0 + L.P - 1) >> L.ps : 1;
-                    launch_estep(est, a.smp, a.N, a.off, C, K, L, first, first + n_items, L.ps_fit, a.ws, s);
+                    estep(first, first + n_items, false);
                     launch_tree(kTreeFit, a.off, a.N, C, K, L, c, c0, c1, a.ws, s, rec32);
                 }
                 hipLaunchKernelGGL(mstep, dim3(1), dim3(64), 0, s, a.off, a.N, L.ps, rec, L.ps_fit, flags, gok, mp, sp,
@@ -889,8 +951,7 @@ static int enqueue_fit(const FitArgs& a, hipStream_t s, const std::vector<int64_
         } else if (a.opts.schedule == SDMM_SCHED_BATCHED) {
             {
                 ScopedTimer tm(SDMM_TIMER_ESTEP, s);
-                launch_estep(est, a.smp, a.N, a.off, C, K, L, 0, (int64_t)C + L.W, L.ps_fit, a.ws, s,
-                             carry_in && it == 0);
+                estep(0, (int64_t)C + L.W, carry_in && it == 0);
             }
             launch_tree(kTreeFit, a.off, a.N, C, K, L, -1, 0, 0, a.ws, s, rec32);
             {

@@ -146,6 +146,36 @@ def test_schedules_and_graph_are_bitwise_equal_and_deterministic(dev, orc):
             assert np.array_equal(st[k], runs[0][1][k], equal_nan=True), k
 
 
+@pytest.mark.parametrize("K,opt", [(3, {}), (16, {}), (16, {"min_range": 2048}), (16, {"min_range": 2048, "flags": 4}),
+                                   (12, {"flags": 2}), (16, {"flags": 1}), (33, {"min_range": 512}), (24, {"flags": 8})])
+def test_few_work_items_give_bitwise_the_results_of_many(dev, orc, K, opt):
+    """A launch of few work items takes the wide E-step (one work group per item) and, with
+    cells of many records, the wide M-step (one group per cell). Cells about the sizes of a
+    step, an item, a block of records and the record tree, fitted in a small batch, must
+    equal bit for bit the same cells in a batch of 700 more, which takes one wave per item
+    and packed M-steps; items of 2048 samples fold their block sums."""
+    print("case: few work items against many", K, opt, flush=True)
+    counts = [0, 1, 15, 17, 63, 64, 65, 255, 256, 257, 511, 4097, 33000]
+    n = len(counts)
+    every = np.array(counts + [20] * 700)
+    rng = np.random.default_rng(3)
+    lo, size = rng.random((every.size, 3)), np.full((every.size, 3), 0.1)
+    b = synth.make_batch(17, every, lo, size, synth.planted_lobes(5))
+    mix0 = synth.initial_mixtures(lo, size, K)
+    few = synth.Batch(np.ascontiguousarray(b.samples[:, :sum(counts)]), b.offsets[:n + 1].copy(), b.lobe)
+    got = []
+    for batch, C in ((few, n), (b, every.size)):
+        m0 = {k: v.reshape(every.size, -1)[:C].reshape(-1).copy() for k, v in mix0.items()}
+        gm, gst = to_torch(m0), state_to_torch(orc.new_state(C, K))
+        s = _gpu_fit(dev, batch, gm, gst, K=K, iters=2, **opt)
+        got.append((to_numpy(gm), to_numpy(gst), s, C))
+    (m1, st1, s1, c1), (m2, st2, s2, c2) = got
+    assert (s1 == s2[:n]).all() and s1[-1] == 0
+    for a, c in ((m1, m2), (st1, st2)):
+        for k in a:
+            assert np.array_equal(a[k].reshape(c1, -1), c[k].reshape(c2, -1)[:n], equal_nan=True), k
+
+
 def test_graph_replays_match_eager(dev, orc):
     print("case: repeated graph replays vs eager", flush=True)
     wl = synth.workload("cells4k", scale=27 / 4096)
