@@ -150,7 +150,11 @@ __device__ __forceinline__ void sample_one(const float* T, bool usable, float wk
 // ---------------------------------------------------------------------------------
 // kernels: the loop trip count is uniform per wave so every group reaches the DPP steps
 // ---------------------------------------------------------------------------------
-template <int G>
+// A wave takes U rounds of S queries at a time, all their loads issued before the first
+// round is computed: one round's chain (cell index, 20 floats of the component's row,
+// stores) leaves too little in flight (500009 queries in path order over 4096 cells: U = 1
+// 52.8 us, U = 4 50.4 us, 640 MB of rows at 12.7 TB/s; the table, 8 MB, is past one L2).
+template <int G, int U>
 __global__ __launch_bounds__(256) void condition_kernel(const float* __restrict__ table, int C, int K,
                                                         const float* __restrict__ qpos, const int32_t* __restrict__ qcell,
                                                         int64_t nq, float* __restrict__ cw, float* __restrict__ cm)
@@ -159,27 +163,48 @@ __global__ __launch_bounds__(256) void condition_kernel(const float* __restrict_
     const int lane = threadIdx.x & 63, comp = lane % G, slot = lane / G;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t q0 = wave * S; q0 < nq; q0 += nwaves * S) {
-        const int64_t q = q0 + slot;
-        const bool inq = q < nq;
-        const int qc = inq ? qcell[q] : 0;
-        const bool usable = inq && qc >= 0 && qc < C;
-        float T[kCond];
-        load_row(table_row(table, qc, K, comp, usable), K, T);
-        const int64_t qq = inq ? q : 0;
-        float m0, m1;
-        float lw = cond_component(T, qpos[qq], qpos[nq + qq], qpos[2 * nq + qq], m0, m1);
-        if (comp >= K || !usable) lw = -INFINITY;
-        const float wk = cond_weight<G>(lw);
-        if (inq && comp < K) {
-            cw[q * K + comp] = wk;
-            cm[(q * K + comp) * 2] = usable ? m0 : 0.0f;
-            cm[(q * K + comp) * 2 + 1] = usable ? m1 : 0.0f;
+    for (int64_t q0 = wave * (S * U); q0 < nq; q0 += nwaves * (S * U)) {
+        int qc[U];
+        float x[U][3], T[U][kCond];
+        bool usable[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = min(q0 + u * S + slot, nq - 1);
+            qc[u] = qcell[q];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) x[u][d] = qpos[d * nq + q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            usable[u] = q0 + u * S + slot < nq && qc[u] >= 0 && qc[u] < C;
+            load_row(table_row(table, qc[u], K, comp, usable[u]), K, T[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = q0 + u * S + slot;
+            float m0, m1;
+            float lw = cond_component(T[u], x[u][0], x[u][1], x[u][2], m0, m1);
+            if (comp >= K || !usable[u]) lw = -INFINITY;
+            const float wk = cond_weight<G>(lw);
+            if (q < nq && comp < K) {
+                cw[q * K + comp] = wk;
+                reinterpret_cast<float2*>(cm)[q * K + comp] =
+                    usable[u] ? make_float2(m0, m1) : make_float2(0.0f, 0.0f);
+            }
         }
     }
 }
 
-template <int G>
+// p / n for the draws or directions of a query (n the same in every lane): 32-bit division
+// where both fit, which takes a quarter of the instructions of the 64-bit one
+__device__ __forceinline__ int64_t query_of(int64_t p, int n, bool small)
+{
+    if (n == 1) return p;
+    return small ? (int64_t)((uint32_t)p / (uint32_t)n) : p / n;
+}
+
+// U rounds of S directions at a time, as in condition_kernel
+template <int G, int U>
 __global__ __launch_bounds__(256) void pdf_kernel(const float* __restrict__ table, int C, int K,
                                                   const int32_t* __restrict__ qcell, int64_t nq,
                                                   const float* __restrict__ cw, const float* __restrict__ cm, int nd,
@@ -187,24 +212,39 @@ __global__ __launch_bounds__(256) void pdf_kernel(const float* __restrict__ tabl
 {
     constexpr int S = 64 / G;
     const int lane = threadIdx.x & 63, comp = lane % G, slot = lane / G;
+    const int kk = comp < K ? comp : K - 1;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t np = nq * nd;
-    for (int64_t p0 = wave * S; p0 < np; p0 += nwaves * S) {
-        const int64_t p = p0 + slot;
-        const bool inp = p < np;
-        const int64_t pp = inp ? p : 0;
-        const int64_t q = pp / nd;
-        const int qc = qcell[q];
-        const bool usable = inp && qc >= 0 && qc < C && comp < K;
-        float T[kCond];
-        load_row(table_row(table, qc, K, comp, usable), K, T);
-        const int kk = comp < K ? comp : K - 1;
-        const float wk = usable ? cw[q * K + kk] : 0.0f;
-        const float m0 = cm[(q * K + kk) * 2], m1 = cm[(q * K + kk) * 2 + 1];
-        const float c = pdf_component(T, pdf_log_const(T, wk), m0, m1, dirs[pp], dirs[np + pp], dirs[2 * np + pp]);
-        const float tot = group_sum<G>(usable ? c : 0.0f);
-        if (inp && comp == 0) pdf_out[p] = tot;
+    const bool small = np <= (int64_t)UINT32_MAX;
+    for (int64_t p0 = wave * (S * U); p0 < np; p0 += nwaves * (S * U)) {
+        int qc[U];
+        float w[U][3], T[U][kCond], wk[U];
+        float2 m[U];
+        bool usable[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = min(p0 + u * S + slot, np - 1);
+            const int64_t q = query_of(p, nd, small);
+            qc[u] = qcell[q];
+            wk[u] = cw[q * K + kk];
+            m[u] = reinterpret_cast<const float2*>(cm)[q * K + kk];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) w[u][d] = dirs[d * np + p];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            usable[u] = p0 + u * S + slot < np && qc[u] >= 0 && qc[u] < C && comp < K;
+            load_row(table_row(table, qc[u], K, comp, usable[u]), K, T[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = p0 + u * S + slot;
+            const float c = pdf_component(T[u], pdf_log_const(T[u], usable[u] ? wk[u] : 0.0f), m[u].x, m[u].y, w[u][0],
+                                          w[u][1], w[u][2]);
+            const float tot = group_sum<G>(usable[u] ? c : 0.0f);
+            if (p < np && comp == 0) pdf_out[p] = tot;
+        }
     }
 }
 
@@ -225,7 +265,7 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ t
         const int64_t d = d0 + slot;
         const bool ind = d < nd;
         const int64_t dd = ind ? d : 0;
-        const int64_t q = dd / ns;
+        const int64_t q = query_of(dd, ns, nd <= (int64_t)UINT32_MAX);
         const int qc = qcell[q];
         const bool usable = ind && qc >= 0 && qc < C;
         float T[kCond];
@@ -339,10 +379,13 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_kernel(const float* __res
     }
 }
 
-// The same conditioning, draws and pdf as cond_sample_pdf_kernel, in three wave-local
-// phases over QB = S * NQR queries, NQR rounds of S queries with QB * ns <= 64 draws:
-//   A. conditioning, lane = (query slot, component), per round: pi', the CDF of pi' and
-//      m into LDS, with each query's cell and last component of positive weight;
+constexpr int kLanesRounds = 4;  // most rounds of S queries per pass
+
+// The same draws and pdf as cond_sample_pdf_kernel and sample_kernel, in three wave-local
+// phases over QB = S * nqr queries, nqr rounds of S queries with QB * ns <= 64 draws:
+//   A. lane = (query slot, component), per round: pi' and m, conditioned here or (Given)
+//      read from the caller's arrays, and the CDF of pi' into LDS, with each query's cell
+//      and last component of positive weight;
 //   B. the draws, one per lane: uniforms, the component by the CDF, the candidate from
 //      the table row of that component;
 //   C. the pdf, lane = (query slot, component) again: every draw of the query over all
@@ -351,76 +394,120 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_kernel(const float* __res
 // computed by the same arithmetic as in sample_one (the scan, the first CDF entry above
 // u0, draw_candidate), so they are the same; the pdf sums over the components may
 // associate differently (FP32 rounding).
-template <int G>
-__global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(const float* __restrict__ table, int C, int K,
-                                                                    const float* __restrict__ qpos,
-                                                                    const int32_t* __restrict__ qcell, int64_t nq,
-                                                                    int ns, int nqr, const float* __restrict__ uniforms,
-                                                                    uint64_t seed, float* __restrict__ dirs_out,
-                                                                    float* __restrict__ pdf_out,
-                                                                    uint8_t* __restrict__ valid_out)
+template <int G, bool Given>
+__global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(
+    const float* __restrict__ table, int C, int K, const float* __restrict__ qpos, const float* __restrict__ cw,
+    const float* __restrict__ cm, const int32_t* __restrict__ qcell, int64_t nq, int ns, int nqr,
+    const float* __restrict__ uniforms, uint64_t seed, float* __restrict__ dirs_out, float* __restrict__ pdf_out,
+    uint8_t* __restrict__ valid_out, int32_t* __restrict__ comp_out)
 {
-    constexpr int S = 64 / G, QBMAX = 4 * S, WPB = 4;
+    constexpr int S = 64 / G, QBMAX = kLanesRounds * S, WPB = 4;
     // per wave: the CDF of pi' (-inf past K and for unusable queries, so that no draw
-    // picks those lanes), the pdf's log constants and the conditioned means of its
-    // queries' components; each query's cell (-1: none) and last component of positive
-    // weight; the draws' directions and validity
+    // picks those lanes), pi' and the conditioned means of its queries' components; each
+    // query's cell (-1: none) and last component of positive weight; the draws' directions
+    // and validity
     __shared__ __align__(16) float cdf_s[WPB][QBMAX][G];
-    __shared__ float lc_s[WPB][QBMAX][G], m0_s[WPB][QBMAX][G], m1_s[WPB][QBMAX][G];
+    __shared__ float wk_s[WPB][QBMAX][G], m0_s[WPB][QBMAX][G], m1_s[WPB][QBMAX][G];
     __shared__ int last_s[WPB][QBMAX], cell_s[WPB][QBMAX];
     __shared__ float4 w_s[WPB][64];
     __shared__ int valid_s[WPB][64];
     const int lane = threadIdx.x & 63, comp = lane % G, slot = lane / G, base = lane - comp;
+    const int kk = comp < K ? comp : K - 1;
     const int wv = threadIdx.x >> 6;
     const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << base);
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t nd = nq * ns;
     const int QB = S * nqr;
-    // the lane's table row stays in registers while its queries' cell repeats (queries
-    // sorted by cell mostly share one); `row_cell` is the cell it holds
-    float T[kCond];
-    int row_cell = -1;
-    auto row_for = [&](int cell) {
-        if (cell != row_cell) {
-            load_row(table_row(table, cell, K, comp, true), K, T);
-            row_cell = cell;
-        }
+    // Phases A and C read different chunks of the lane's table row, only 2 and 7 both. Each
+    // loads what it reads, again only when its round's cell changes (queries sorted by cell
+    // mostly share one), and keeps nothing for the other, so five waves fit a SIMD. C's
+    // first row and the next pass's first queries are loaded ahead. Rows loaded whole by
+    // each phase took 308 us for 1M queries of one draw in path order over 4096 cells, this
+    // 188 us; 2^22 queries of four draws sorted by cell 501 and 484 us.
+    auto load_chunks = [&](float (&T)[kCond], int cell, auto... q) {
+        const float4* row = reinterpret_cast<const float4*>(table_row(table, cell, K, comp, true));
+        (
+            [&] {
+                const float4 v = row[(int64_t)q * K];
+                T[4 * q] = v.x;
+                T[4 * q + 1] = v.y;
+                T[4 * q + 2] = v.z;
+                T[4 * q + 3] = v.w;
+            }(),
+            ...);
     };
+    // a round's queries: cell and position (or nothing to condition)
+    struct Query {
+        int cell;
+        float x0, x1, x2;
+    };
+    auto load_query = [&](int64_t q) {
+        const int64_t qq = q < nq ? q : 0;
+        Query u{qcell[qq], 0.0f, 0.0f, 0.0f};
+        if constexpr (!Given) {
+            u.x0 = qpos[qq];
+            u.x1 = qpos[nq + qq];
+            u.x2 = qpos[2 * nq + qq];
+        }
+        return u;
+    };
+    Query first_q{};  // of the pass's first round, loaded before the pass before it ends
+    if (wave * QB < nq) first_q = load_query(wave * QB + slot);
     for (int64_t qb = wave * QB; qb < nq; qb += nwaves * QB) {
         // A: conditioning
-        for (int r = 0; r < nqr; ++r) {
-            const int qi = r * S + slot;
-            const int64_t q = qb + qi;
-            const bool inq = q < nq;
-            const int64_t qq = inq ? q : 0;
-            const int qc = qcell[qq];
-            const bool usable = inq && qc >= 0 && qc < C;
-            row_for(usable ? qc : 0);
-            float m0, m1;
-            float lw = cond_component(T, qpos[qq], qpos[nq + qq], qpos[2 * nq + qq], m0, m1);
-            if (comp >= K || !usable) lw = -INFINITY;
-            const float wk = cond_weight<G>(lw);
-            const float cdf = group_inclusive_scan<G>(wk);
-            const uint64_t pos = __ballot(comp < K && usable && wk > 0.0f) & gmask;
-            cdf_s[wv][qi][comp] = (comp < K && usable) ? cdf : -INFINITY;
-            lc_s[wv][qi][comp] = pdf_log_const(T, wk);
-            m0_s[wv][qi][comp] = m0;
-            m1_s[wv][qi][comp] = m1;
-            if (comp == 0) {
-                last_s[wv][qi] = pos ? 63 - __builtin_clzll(pos) - base : -1;
-                cell_s[wv][qi] = usable ? qc : -1;
+        int cell0 = 0;  // the first round's cell
+        {
+            float T[kCond];
+            int row_cell;
+            for (int r = 0; r < nqr; ++r) {
+                const int qi = r * S + slot;
+                const int64_t q = qb + qi;
+                const bool inq = q < nq;
+                const int64_t qq = inq ? q : 0;
+                const Query u = r == 0 ? first_q : load_query(q);
+                const bool usable = inq && u.cell >= 0 && u.cell < C;
+                const int cell = usable ? u.cell : 0;
+                float m0, m1, wk;
+                if constexpr (Given) {
+                    wk = (usable && comp < K) ? cw[qq * K + kk] : 0.0f;
+                    const float2 m = reinterpret_cast<const float2*>(cm)[qq * K + kk];
+                    m0 = m.x;
+                    m1 = m.y;
+                } else {
+                    if (r == 0 || cell != row_cell) load_chunks(T, cell, 2, 3, 4, 5, 7);
+                    row_cell = cell;
+                    float lw = cond_component(T, u.x0, u.x1, u.x2, m0, m1);
+                    if (comp >= K || !usable) lw = -INFINITY;
+                    wk = cond_weight<G>(lw);
+                }
+                if (r == 0) cell0 = cell;
+                const float cdf = group_inclusive_scan<G>(wk);
+                const uint64_t pos = __ballot(comp < K && usable && wk > 0.0f) & gmask;
+                cdf_s[wv][qi][comp] = (comp < K && usable) ? cdf : -INFINITY;
+                wk_s[wv][qi][comp] = wk;
+                m0_s[wv][qi][comp] = m0;
+                m1_s[wv][qi][comp] = m1;
+                if (comp == 0) {
+                    last_s[wv][qi] = pos ? 63 - __builtin_clzll(pos) - base : -1;
+                    cell_s[wv][qi] = usable ? cell : -1;
+                }
             }
         }
+        // the first round's row for C is on its way during B
+        float T[kCond];
+        load_chunks(T, cell0, 0, 1, 2, 6, 7);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // this wave's LDS writes are done
         // B: one draw per lane
         {
-            const int qi = lane / ns, t = lane % ns;
-            const int64_t q = qb + qi;
-            const bool act = qi < QB && q < nq;
-            const int64_t d = act ? q * ns + t : 0;
+            uint64_t key = seed;
+            int64_t ndo = nd;
+            asm volatile("" : "+s"(key), "+s"(ndo));
+            const int qi = lane / ns;
+            const bool act = qi < QB && qb + qi < nq;
+            const int64_t d = act ? qb * ns + lane : 0;  // the pass's draws are contiguous
             float u0, u1, u2;
-            draw_uniforms(uniforms, nd, d, seed, u0, u1, u2);
+            draw_uniforms(uniforms, ndo, d, key, u0, u1, u2);
             const int qis = act ? qi : 0;
             const int qc = cell_s[wv][qis];
             // the first component whose CDF value exceeds u0, else the last of positive weight
@@ -452,47 +539,56 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(const float*
             const int valid = act && sel >= 0 && ok;
             w_s[wv][lane] = make_float4(w[0], w[1], w[2], 0.0f);
             valid_s[wv][lane] = valid;
-            if (act) {  // the pass's draws are contiguous: d = qb * ns + lane
+            if (act) {
                 dirs_out[d] = valid ? w[0] : 0.0f;
-                dirs_out[nd + d] = valid ? w[1] : 0.0f;
-                dirs_out[2 * nd + d] = valid ? w[2] : 0.0f;
+                dirs_out[ndo + d] = valid ? w[1] : 0.0f;
+                dirs_out[2 * ndo + d] = valid ? w[2] : 0.0f;
                 valid_out[d] = (uint8_t)valid;
+                if constexpr (Given)
+                    if (comp_out) comp_out[d] = sel;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         // C: the pdf of every draw over all components, outputs
+        const int64_t qn = qb + nwaves * QB;
+        if (qn < nq) first_q = load_query(qn + slot);
+        int row_cell = cell0;
         for (int r = 0; r < nqr; ++r) {
             const int qi = r * S + slot;
             const int64_t q = qb + qi;
             const bool inq = q < nq;
             const int qc = cell_s[wv][qi];
-            row_for(qc >= 0 ? qc : 0);
-            const float lc = lc_s[wv][qi][comp], m0 = m0_s[wv][qi][comp], m1 = m1_s[wv][qi][comp];
+            const int cell = qc >= 0 ? qc : 0;
+            if (cell != row_cell) load_chunks(T, cell, 0, 1, 2, 6, 7);
+            row_cell = cell;
+            const float lc = pdf_log_const(T, wk_s[wv][qi][comp]), m0 = m0_s[wv][qi][comp], m1 = m1_s[wv][qi][comp];
             float pdf = 0.0f;
             for (int tt = 0; tt < ns; tt += 4) {  // wave-uniform
-                float c[4];
                 const float4* wq = &w_s[wv][qi * ns + tt];
                 if (tt + 4 <= ns) {  // four draws of this query
+                    float c[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) c[j] = pdf_component(T, lc, m0, m1, wq[j].x, wq[j].y, wq[j].z);
-                } else {  // the last ones, repeated up to four
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float4 wd = wq[min(j, ns - 1 - tt)];
-                        c[j] = pdf_component(T, lc, m0, m1, wd.x, wd.y, wd.z);
+                    for (int j = 0; j < 4; ++j) c[j] = comp < K ? c[j] : 0.0f;
+                    if constexpr (G == 16) {
+                        // the four sums over the row at once: lane comp ends with the sum for
+                        // draw tt + (comp & 3) (group_sum4_row16), kept by the quad of that draw
+                        const float p = group_sum4_row16(c);
+                        pdf = (comp >> 2) == (tt >> 2) ? p : pdf;
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float p = group_sum<G>(c[j]);
+                            pdf = comp == tt + j ? p : pdf;
+                        }
                     }
-                }
+                } else {  // the last ones
 #pragma unroll
-                for (int j = 0; j < 4; ++j) c[j] = comp < K ? c[j] : 0.0f;
-                if constexpr (G == 16) {
-                    // the four sums over the row at once: lane comp ends with the sum for
-                    // draw tt + (comp & 3) (group_sum4_row16), kept by the quad of that draw
-                    const float p = group_sum4_row16(c);
-                    pdf = (comp >> 2) == (tt >> 2) ? p : pdf;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float p = group_sum<G>(c[j]);
+                    for (int j = 0; j < 3; ++j) {
+                        if (tt + j >= ns) break;  // wave-uniform
+                        const float c = pdf_component(T, lc, m0, m1, wq[j].x, wq[j].y, wq[j].z);
+                        const float p = group_sum<G>(comp < K ? c : 0.0f);
                         pdf = comp == tt + j ? p : pdf;
                     }
                 }
@@ -501,6 +597,21 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(const float*
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // before the next pass overwrites
     }
+}
+
+// rounds per pass of the condition and pdf kernels, and the wave groups below which a launch
+// keeps one round per wave (four waves per SIMD, so that a small call spreads out)
+constexpr int kRounds = 4;
+constexpr int64_t kFewGroups = 4096;
+
+// rounds of S queries that share one pass of the draws: as many as fill its 64 lanes, at
+// most kLanesRounds (more take the LDS of one wave less per SIMD: 4% slower in path order),
+// fewer where the call is too small to give every SIMD four waves of that many
+static int lanes_rounds(int64_t nq, int S, int ns)
+{
+    int nqr = std::max(1, std::min(kLanesRounds, 64 / (S * ns)));
+    while (nqr > 1 && nq < kFewGroups * S * nqr) nqr >>= 1;
+    return nqr;
 }
 
 }  // namespace sdmm
@@ -526,8 +637,13 @@ extern "C" int sdmm_condition(const float* table, int32_t n_cells, int32_t K, co
     if (!qpos || !qcell || !cond_w || !cond_m) return SDMM_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K);
-    SDMM_DISPATCH_G(G, (condition_kernel<g><<<grid_for(nq, 64 / g), 256, 0, s>>>(table, n_cells, K, qpos, qcell,
-                                                                                  nq, cond_w, cond_m)));
+    const int S = 64 / G;
+    if (nq >= kFewGroups * S * kRounds)
+        SDMM_DISPATCH_G(G, (condition_kernel<g, kRounds><<<grid_for(nq, S * kRounds), 256, 0, s>>>(
+                               table, n_cells, K, qpos, qcell, nq, cond_w, cond_m)))
+    else
+        SDMM_DISPATCH_G(G, (condition_kernel<g, 1><<<grid_for(nq, S), 256, 0, s>>>(table, n_cells, K, qpos, qcell, nq,
+                                                                                   cond_w, cond_m)))
     return check(hipGetLastError());
 }
 
@@ -540,8 +656,13 @@ extern "C" int sdmm_pdf(const float* table, int32_t n_cells, int32_t K, const in
     if (!qcell || !cond_w || !cond_m || !dirs || !pdf_out) return SDMM_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K);
-    SDMM_DISPATCH_G(G, (pdf_kernel<g><<<grid_for(nq * nd, 64 / g), 256, 0, s>>>(table, n_cells, K, qcell, nq, cond_w,
-                                                                                 cond_m, nd, dirs, pdf_out)));
+    const int S = 64 / G;
+    if (nq * nd >= kFewGroups * S * kRounds)
+        SDMM_DISPATCH_G(G, (pdf_kernel<g, kRounds><<<grid_for(nq * nd, S * kRounds), 256, 0, s>>>(
+                               table, n_cells, K, qcell, nq, cond_w, cond_m, nd, dirs, pdf_out)))
+    else
+        SDMM_DISPATCH_G(G, (pdf_kernel<g, 1><<<grid_for(nq * nd, S), 256, 0, s>>>(table, n_cells, K, qcell, nq, cond_w,
+                                                                                  cond_m, nd, dirs, pdf_out)))
     return check(hipGetLastError());
 }
 
@@ -555,9 +676,20 @@ extern "C" int sdmm_sample(const float* table, int32_t n_cells, int32_t K, const
     if (!qcell || !cond_w || !cond_m || !dirs_out || !pdf_out || !valid_out) return SDMM_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K);
-    SDMM_DISPATCH_G(G, (sample_kernel<g><<<grid_for(nq * ns, 64 / g), 256, 0, s>>>(
-                           table, n_cells, K, qcell, nq, cond_w, cond_m, ns, uniforms, seed, dirs_out, pdf_out,
-                           valid_out, comp_out)));
+    const int S = 64 / G;
+    // a table that fits one XCD's L2 (4 MB): the lanes kernel, which reads the picked
+    // component's row once more per draw; from a larger one and in path order those reads
+    // cost more than they save (500009 queries, 8 MB: 79.9 against 61.7 us)
+    if (S * ns <= 64 && (int64_t)n_cells * K * kCond * (int64_t)sizeof(float) <= (4 << 20)) {
+        const int nqr = lanes_rounds(nq, S, ns);
+        SDMM_DISPATCH_G(G, (cond_sample_pdf_lanes_kernel<g, true><<<grid_for(nq, S * nqr), 256, 0, s>>>(
+                               table, n_cells, K, nullptr, cond_w, cond_m, qcell, nq, ns, nqr, uniforms, seed, dirs_out,
+                               pdf_out, valid_out, comp_out)));
+    } else {
+        SDMM_DISPATCH_G(G, (sample_kernel<g><<<grid_for(nq * ns, 64 / g), 256, 0, s>>>(
+                               table, n_cells, K, qcell, nq, cond_w, cond_m, ns, uniforms, seed, dirs_out, pdf_out,
+                               valid_out, comp_out)));
+    }
     return check(hipGetLastError());
 }
 
@@ -574,11 +706,10 @@ extern "C" int sdmm_condition_sample_pdf(const float* table, int32_t n_cells, in
     ScopedTimer tm(SDMM_TIMER_QUERY, s);
     const int S = 64 / G;
     if (S * ns <= 64) {
-        // draws of up to four rounds of S queries share one pass of the draw phase
-        const int nqr = std::max(1, std::min(4, 64 / (S * ns)));
-        SDMM_DISPATCH_G(G, (cond_sample_pdf_lanes_kernel<g><<<grid_for(nq, S * nqr), 256, 0, s>>>(
-                               table, n_cells, K, qpos, qcell, nq, ns, nqr, uniforms, seed, dirs_out, pdf_out,
-                               valid_out)));
+        const int nqr = lanes_rounds(nq, S, ns);
+        SDMM_DISPATCH_G(G, (cond_sample_pdf_lanes_kernel<g, false><<<grid_for(nq, S * nqr), 256, 0, s>>>(
+                               table, n_cells, K, qpos, nullptr, nullptr, qcell, nq, ns, nqr, uniforms, seed, dirs_out,
+                               pdf_out, valid_out, nullptr)));
     } else {
         SDMM_DISPATCH_G(G, (cond_sample_pdf_kernel<g><<<grid_for(nq, 64 / g), 256, 0, s>>>(
                                table, n_cells, K, qpos, qcell, nq, ns, uniforms, seed, dirs_out, pdf_out, valid_out)));

@@ -159,6 +159,57 @@ def test_device_generator_matches_the_oracle_generator(dev, orc, fitted):
     assert dev.equal(fv1, v1)
 
 
+@pytest.mark.parametrize("K,ns,nq", [(16, 4, 70001), (16, 1, 66001), (16, 16, 20011), (16, 17, 1001), (12, 5, 17003),
+                                     (5, 2, 140001), (33, 3, 17001), (24, 1, 33003)])
+def test_large_calls_equal_their_parts_bitwise(dev, K, ns, nq):
+    """Calls large enough for several rounds per wave pass, on queries in arbitrary order
+    with some cells out of range, against the same queries in parts that are too small for
+    it: conditioning, pdf, separate and fused draws are bitwise equal. The draws of
+    a table that fits one L2 (lanes kernel) equal those of the same mixtures inside a table
+    that does not (group kernel); their pdfs may associate differently: K FP32 terms of
+    one sign, relative 2^-23 K."""
+    print("case: large query calls", K, ns, nq, flush=True)
+    from paper_2111_13094_amd import sdmm
+    C = 40
+    rng = np.random.default_rng(K + ns)
+    lo = rng.random((C, 3))
+    mix = synth.initial_mixtures(lo, np.full((C, 3), 0.3), K)
+    mix["cov"] = (mix["cov"].reshape(C * K, 15) * rng.uniform(0.05, 1.0, (C * K, 1))).reshape(-1)
+    mix["pi"] = rng.dirichlet(np.full(K, 2.0), C).reshape(-1)
+    qcell = rng.integers(0, C, nq).astype(np.int32)
+    qpos = (lo[qcell] + 0.3 * rng.random((nq, 3))).astype(np.float32)
+    qcell[rng.integers(0, nq, 5)] = -1
+    qcell[rng.integers(0, nq, 5)] = 4 * C * 32
+    table, qp, qc, cw, cm = _gpu_cond(dev, mix, C, K, qpos, qcell)
+    nd = 2
+    d = rng.normal(size=(nq * nd, 3))
+    gd = dev.from_numpy(np.ascontiguousarray((d / np.linalg.norm(d, axis=1, keepdims=True)).T.astype(np.float32))).cuda()
+    gu = dev.from_numpy(np.ascontiguousarray(synth.make_uniforms(3, nq * ns).T)).cuda()
+    whole = (cw, cm, sdmm.pdf(table, C, K, qc, cw, cm, gd, nd),
+             *sdmm.sample(table, C, K, qc, cw, cm, ns, uniforms=gu, with_comp=True),
+             *sdmm.condition_sample_pdf(table, C, K, qp, qc, ns, uniforms=gu))
+    step = 1999
+    parts = []
+    for a in range(0, nq, step):
+        b = min(nq, a + step)
+        q, c = qp[:, a:b].contiguous(), qc[a:b].contiguous()
+        u = gu[:, a * ns:b * ns].contiguous()
+        w, m = sdmm.condition(table, C, K, q, c)
+        parts.append((w, m, sdmm.pdf(table, C, K, c, w, m, gd[:, a * nd:b * nd].contiguous(), nd),
+                      *sdmm.sample(table, C, K, c, w, m, ns, uniforms=u, with_comp=True),
+                      *sdmm.condition_sample_pdf(table, C, K, q, c, ns, uniforms=u)))
+    axis = [0, 0, 0, 1, 0, 0, 0, 1, 0, 0]
+    for j, x in enumerate(whole):
+        assert dev.equal(x, dev.cat([p[j] for p in parts], dim=axis[j])), j
+    big = 4 * C * 32 // K * 16  # cells of a table over 4 MB
+    wide = dev.zeros(big * K * 32, dtype=dev.float32, device="cuda")
+    wide[:table.numel()] = table
+    qcv = dev.where(qc >= C, dev.full_like(qc, -1), qc)
+    e = sdmm.sample(wide, big, K, qcv, cw, cm, ns, uniforms=gu, with_comp=True)
+    assert dev.equal(e[0], whole[3]) and dev.equal(e[2], whole[5]) and dev.equal(e[3], whole[6])
+    assert dev.allclose(e[1], whole[4], rtol=K * 2.0 ** -23, atol=0)
+
+
 def test_invalid_query_cells_give_zero(dev, orc, fitted):
     print("case: queries with out-of-range cells", flush=True)
     from paper_2111_13094_amd import sdmm
