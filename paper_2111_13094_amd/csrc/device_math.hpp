@@ -66,6 +66,20 @@ __device__ __forceinline__ float group_max(float v)
     return __int_as_float(k ^ ((k >> 31) & 0x7fffffff));
 }
 
+// maximum over the group of values that are not negative (their bits order as integers)
+template <int G>
+__device__ __forceinline__ float group_max_positive(float v)
+{
+    int k = __float_as_int(v);
+    if constexpr (G >= 2) k = dpp_max_i32<kDppXor1>(k);
+    if constexpr (G >= 4) k = dpp_max_i32<kDppXor2>(k);
+    if constexpr (G >= 8) k = dpp_max_i32<kDppHalfMirror>(k);
+    if constexpr (G >= 16) k = dpp_max_i32<kDppMirror>(k);
+    if constexpr (G >= 32) k = max(k, __shfl_xor(k, 16));
+    if constexpr (G >= 64) k = max(k, __shfl_xor(k, 32));
+    return __int_as_float(k);
+}
+
 template <int G>
 __device__ __forceinline__ float group_sum(float v)
 {

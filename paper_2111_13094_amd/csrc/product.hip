@@ -100,6 +100,36 @@ __device__ __forceinline__ BsdfWorld shfl_bsdf(const BsdfWorld& v, int src)
     return o;
 }
 
+// The kept BSDF components of a batch of queries in LDS, those of query qi at 2 qi and
+// 2 qi + 1: log2 weight (-inf: none), and first w[0] as picked {conditioned offset,
+// component, unused}, then all of w rotated
+template <int N>
+struct BsdfStage {
+    float4 w[3][N];
+    float lw[N];
+};
+
+template <int N>
+__device__ __forceinline__ BsdfWorld staged_bsdf(const BsdfStage<N>& st, int i)
+{
+    const float4 a = st.w[0][i], b = st.w[1][i], c = st.w[2][i];
+    BsdfWorld o;
+    o.cx = a.x;
+    o.cy = a.y;
+    o.cz = a.z;
+    o.d[0] = a.w;
+    o.d[1] = b.x;
+    o.d[2] = b.y;
+    o.d[3] = b.z;
+    o.d[4] = b.w;
+    o.d[5] = c.x;
+    o.s00 = c.y;
+    o.s01 = c.z;
+    o.s11 = c.w;
+    o.lw = st.lw[i];
+    return o;
+}
+
 // one product pair in the tangent space of the radiance component (frame R, conditioned
 // offset m, covariance from the table's L')
 struct Pair {
@@ -202,7 +232,40 @@ struct ProductQuery {
     bool any;  // some pair has weight
 };
 
-// Set-up of one query (steps 1-3). Lanes of a group must all call it.
+// Step 3: lane k's pairs of its conditioned component (log2 weight lwk, offset m, covariance
+// a in the frame Qy.R) with the two kept BSDF components, and their probabilities
+template <int G>
+__device__ __forceinline__ void product_pairs(int K, float lwk, float m0, float m1, float a00, float a01, float a11,
+                                              const BsdfWorld& b0, const BsdfWorld& b1, ProductQuery& Qy)
+{
+    const int comp = (threadIdx.x & 63) % G;
+    // pairs and their probabilities
+    Qy.p0 = make_pair(Qy.R, lwk, m0, m1, a00, a01, a11, b0);
+    Qy.p1 = make_pair(Qy.R, lwk, m0, m1, a00, a01, a11, b1);
+    if (comp >= K) Qy.p0.l = Qy.p1.l = -INFINITY;
+    // pair probabilities: exp2 of the log2 weights normalised over the 2K pairs; a group
+    // whose sum leaves [2^-100, 2^100] takes the group maximum first
+    float e0 = __builtin_amdgcn_exp2f(Qy.p0.l), e1 = __builtin_amdgcn_exp2f(Qy.p1.l);
+    float tot = group_sum<G>(e0 + e1);
+    const bool out = !(tot >= 0x1p-100f && tot <= 0x1p100f);
+    Qy.any = true;
+    if (__ballot(out)) {
+        const float lm = group_max<G>(fmaxf(Qy.p0.l, Qy.p1.l));
+        const bool any = lm != -INFINITY;
+        const float f0 = any ? __builtin_amdgcn_exp2f(Qy.p0.l - lm) : 0.0f;
+        const float f1 = any ? __builtin_amdgcn_exp2f(Qy.p1.l - lm) : 0.0f;
+        const float t2 = group_sum<G>(f0 + f1);
+        e0 = out ? f0 : e0;
+        e1 = out ? f1 : e1;
+        tot = out ? t2 : tot;
+        Qy.any = out ? any : true;
+    }
+    const float itot = tot > 0.0f ? __builtin_amdgcn_rcpf(tot) : 0.0f;
+    Qy.P0 = e0 * itot;
+    Qy.P1 = e1 * itot;
+}
+
+// Set-up of one query (steps 1-3), every lane rotating its own BSDF component. Lanes of a group must all call it.
 template <int G>
 __device__ __forceinline__ void product_setup(const float* __restrict__ table, int C, int K,
                                               const float* __restrict__ btable, int CB, int Kb, int qc, int bc,
@@ -244,30 +307,131 @@ __device__ __forceinline__ void product_setup(const float* __restrict__ table, i
     BsdfWorld b1 = shfl_bsdf(mine, base + (s1 < 0 ? 0 : s1));
     if (s0 < 0) b0.lw = -INFINITY;
     if (s1 < 0) b1.lw = -INFINITY;
-    // pairs and their probabilities
-    Qy.p0 = make_pair(Qy.R, lwk, m0, m1, a00, a01, a11, b0);
-    Qy.p1 = make_pair(Qy.R, lwk, m0, m1, a00, a01, a11, b1);
-    if (comp >= K) Qy.p0.l = Qy.p1.l = -INFINITY;
-    // pair probabilities: exp2 of the log2 weights normalised over the 2K pairs; a group
-    // whose sum leaves [2^-100, 2^100] takes the group maximum first
-    float e0 = __builtin_amdgcn_exp2f(Qy.p0.l), e1 = __builtin_amdgcn_exp2f(Qy.p1.l);
-    float tot = group_sum<G>(e0 + e1);
-    const bool out = !(tot >= 0x1p-100f && tot <= 0x1p100f);
-    Qy.any = true;
-    if (__ballot(out)) {
-        const float lm = group_max<G>(fmaxf(Qy.p0.l, Qy.p1.l));
-        const bool any = lm != -INFINITY;
-        const float f0 = any ? __builtin_amdgcn_exp2f(Qy.p0.l - lm) : 0.0f;
-        const float f1 = any ? __builtin_amdgcn_exp2f(Qy.p1.l - lm) : 0.0f;
-        const float t2 = group_sum<G>(f0 + f1);
-        e0 = out ? f0 : e0;
-        e1 = out ? f1 : e1;
-        tot = out ? t2 : tot;
-        Qy.any = out ? any : true;
+    product_pairs<G>(K, lwk, m0, m1, a00, a01, a11, b0, b1, Qy);
+}
+
+// element at a byte offset past a wave-uniform pointer: one load with a scalar base
+template <typename T>
+__device__ __forceinline__ T ld_at(const T* base, uint32_t byte)
+{
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte);
+}
+
+__device__ __forceinline__ bool usable_query(int qc, int C, int bc, int CB)
+{
+    return qc >= 0 && qc < C && bc >= 0 && bc < CB;
+}
+
+// The conditioned BSDF weights of the group from the log2 weights lb (-inf past Kb): the
+// lane's log2 weight, and whether it holds the heaviest component (the lowest lane with
+// the largest weight) or the heaviest of the others; below = the group's lower lanes.
+template <int G>
+__device__ __forceinline__ float pick_heaviest(float lb, bool in, uint64_t below, bool& first, bool& second)
+{
+    float wb;
+    const float lwb = cond_log_weight<G>(lb, wb);
+    const bool cand = in && wb > 0.0f;
+    const float w1 = group_max_positive<G>(wb);  // every lane takes part
+    const bool top = cand && wb == w1;
+    first = top && (__ballot(top) & below) == 0;
+    const float wb2 = first ? 0.0f : wb;
+    const float w2 = group_max_positive<G>(wb2);
+    const bool top2 = cand && !first && wb2 == w2;
+    second = top2 && (__ballot(top2) & below) == 0;
+    return lwb;
+}
+
+template <int G>
+__device__ __forceinline__ uint64_t lanes_below()
+{
+    const int lane = threadIdx.x & 63, base = lane - lane % G;
+    return ((1ull << lane) - 1ull) & ~((1ull << base) - 1ull);
+}
+
+// Keeps the wave's LDS accesses before and after it in program order (the hardware does, a
+// lane's own view would let the compiler move them); it waits for nothing.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The BSDF's share of the set-up (steps 1 and 2) for the queries q0 .. q0 + nr * S - 1 (q0
+// < nq, the same in every lane), nr <= N / (2 S) rounds of S queries: per round the model
+// is conditioned and its two heaviest components leave their offset and weight in LDS;
+// then one lane per kept component, of every round at once, rotates it to world. Saves
+// the rotations of the components that are not kept and their broadcast, at the price of
+// a second chain of loads.
+template <int G, int N>
+__device__ __forceinline__ void stage_bsdf(BsdfStage<N>& st, int C, const int32_t* __restrict__ qcell,
+                                           const float* __restrict__ btable, int CB, int Kb,
+                                           const float* __restrict__ bpar, const int32_t* __restrict__ bcell,
+                                           const float* __restrict__ frames, int64_t nq, int64_t q0, int nr)
+{
+    constexpr int S = 64 / G;
+    const int lane = threadIdx.x & 63, comp = lane % G, slot = lane / G;
+    const uint64_t below = lanes_below<G>();
+    const int n = (int)min((int64_t)(nr * S), nq - q0);
+    for (int r = 0; r < nr; ++r) {
+        const int qi = r * S + slot;
+        const uint32_t o = 4u * (uint32_t)min(qi, n - 1);
+        const int qc = ld_at(qcell + q0, o), bc = ld_at(bcell + q0, o);
+        const bool usable = qi < n && usable_query(qc, C, bc, CB);
+        float TB[kCond];
+        load_row(table_row(btable, bc, Kb, comp, usable), Kb, TB);
+        float bm0, bm1;
+        float lb = cond_component(TB, ld_at(bpar + q0, o), ld_at(bpar + nq + q0, o), ld_at(bpar + 2 * nq + q0, o),
+                                  bm0, bm1);
+        if (comp >= Kb || !usable) lb = -INFINITY;
+        bool first, second;
+        const float lwb = pick_heaviest<G>(lb, comp < Kb, below, first, second);
+        if (comp == 0) {  // none, unless overwritten below
+            st.lw[2 * qi] = st.lw[2 * qi + 1] = -INFINITY;
+            st.w[0][2 * qi] = st.w[0][2 * qi + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        wave_order();
+        if (first || second) {
+            const int at = 2 * qi + (second ? 1 : 0);
+            st.lw[at] = lwb;
+            st.w[0][at] = make_float4(bm0, bm1, __int_as_float(comp), 0.0f);
+        }
     }
-    const float itot = tot > 0.0f ? __builtin_amdgcn_rcpf(tot) : 0.0f;
-    Qy.P0 = e0 * itot;
-    Qy.P1 = e1 * itot;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // this wave's LDS writes are done
+    if (lane < 2 * S * nr) {
+        const uint32_t o = 4u * (uint32_t)min(lane >> 1, n - 1);
+        const int bc = ld_at(bcell + q0, o);
+        const float4 pick = st.w[0][lane];
+        float F[9], TB[kCond];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) F[i] = ld_at(frames + i * nq + q0, o);
+        load_row(table_row(btable, bc, Kb, __float_as_int(pick.z), bc >= 0 && bc < CB), Kb, TB);
+        const BsdfWorld w = rotate_bsdf(TB, pick.x, pick.y, F, 0.0f);
+        st.w[0][lane] = make_float4(w.cx, w.cy, w.cz, w.d[0]);
+        st.w[1][lane] = make_float4(w.d[1], w.d[2], w.d[3], w.d[4]);
+        st.w[2][lane] = make_float4(w.d[5], w.s00, w.s01, w.s11);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+}
+
+// Set-up of one query (steps 1-3) whose kept BSDF components are staged at 2 qi; qc its cell
+template <int G, int N>
+__device__ __forceinline__ void product_setup_staged(const float* __restrict__ table, int K, int qc, bool usable,
+                                                     float x0, float x1, float x2, const BsdfStage<N>& st, int qi,
+                                                     ProductQuery& Qy)
+{
+    const int comp = (threadIdx.x & 63) % G;
+    float T[kCond];
+    load_row(table_row(table, qc, K, comp, usable), K, T);
+    float m0, m1;
+    float lw = cond_component(T, x0, x1, x2, m0, m1);
+    if (comp >= K || !usable) lw = -INFINITY;
+    float wk_unused;
+    const float lwk = cond_log_weight<G>(lw, wk_unused);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Qy.R[i] = T[i];
+    const float l0 = T[24], l1 = T[25], l2 = T[26];
+    const float a00 = l0 * l0, a01 = l0 * l1, a11 = fmaf(l1, l1, l2 * l2);
+    product_pairs<G>(K, lwk, m0, m1, a00, a01, a11, staged_bsdf(st, 2 * qi), staged_bsdf(st, 2 * qi + 1), Qy);
 }
 
 // the lane's share of the density of the normalised product mixture at a world direction
@@ -615,6 +779,17 @@ __global__ __launch_bounds__(64 * kProdWpb) void product_sample_lanes_kernel(
     }
 }
 
+// The pdf is bound by vector issue: 657 instructions per wave and four queries with one
+// direction, of which the rotation of all 16 lanes' BSDF components, two of them kept, and
+// the broadcast of these two take about 110. Staged they are shared by 32 queries: 2 M
+// queries of K = Kb = 16 take 485-510 us instead of 585-620. It needs calls that give every
+// SIMD four waves of that many, to hide the second chain of loads: 131,072 queries are level
+// (draws and pdf 86 us), with passes of 16 queries 60,000 lose 2% and 33,000 13%.
+// Draws do not stage: their pairs' LDS leaves fewer waves then (60,000 queries of 4 draws 8%
+// slower, 2 M no faster).
+constexpr int kStagedQueries = 32;
+constexpr int64_t kStagedCall = 131072;
+
 template <int G>
 __global__ __launch_bounds__(256) void product_pdf_kernel(
     const float* __restrict__ table, int C, int K, const float* __restrict__ qpos, const int32_t* __restrict__ qcell,
@@ -641,6 +816,45 @@ __global__ __launch_bounds__(256) void product_pdf_kernel(
             const float v = product_density<G>(Qy, K, dirs[p], dirs[np + p], dirs[2 * np + p]);
             if (inq && comp == 0) pdf_out[p] = Qy.any ? v : 0.0f;
         }
+    }
+}
+
+// The same with the BSDF components of nr rounds of S queries staged together (32 queries)
+template <int G>
+__global__ __launch_bounds__(256) void product_pdf_staged_kernel(
+    const float* __restrict__ table, int C, int K, const float* __restrict__ qpos, const int32_t* __restrict__ qcell,
+    const float* __restrict__ btable, int CB, int Kb, const float* __restrict__ bpar,
+    const int32_t* __restrict__ bcell, const float* __restrict__ frames, int64_t nq, int nd,
+    const float* __restrict__ dirs, float* __restrict__ pdf_out)
+{
+    constexpr int S = 64 / G, nr = kStagedQueries / S, WPB = 4;
+    __shared__ BsdfStage<2 * kStagedQueries> stage_s[WPB];
+    const int lane = threadIdx.x & 63, comp = lane % G, slot = lane / G;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    BsdfStage<2 * kStagedQueries>& st = stage_s[wv];
+    const int64_t wave = (int64_t)blockIdx.x * WPB + wv, nwaves = (int64_t)gridDim.x * WPB;
+    const int64_t np = nq * nd;
+    for (int64_t q0 = wave * kStagedQueries; q0 < nq; q0 += nwaves * kStagedQueries) {
+        const int n = (int)min((int64_t)kStagedQueries, nq - q0);
+        stage_bsdf<G>(st, C, qcell, btable, CB, Kb, bpar, bcell, frames, nq, q0, nr);
+        for (int r = 0; r < nr; ++r) {
+            const int qi = r * S + slot, qj = min(qi, n - 1);
+            const uint32_t o = 4u * (uint32_t)qj;
+            const int qc = ld_at(qcell + q0, o), bc = ld_at(bcell + q0, o);
+            ProductQuery Qy;
+            product_setup_staged<G>(table, K, qc, qi < n && usable_query(qc, C, bc, CB), ld_at(qpos + q0, o),
+                                    ld_at(qpos + nq + q0, o), ld_at(qpos + 2 * nq + q0, o), st, qj, Qy);
+            // the query's first direction, past the batch's
+            const int64_t p0 = q0 * nd;
+            const uint64_t p = (uint64_t)(uint32_t)qj * (uint32_t)nd;
+            const float *dx = dirs + p0 + p, *dy = dirs + np + p0 + p, *dz = dirs + 2 * np + p0 + p;
+            float* out = pdf_out + p0 + p;
+            for (int t = 0; t < nd; ++t) {
+                const float v = product_density<G>(Qy, K, dx[t], dy[t], dz[t]);
+                if (qi < n && comp == 0) out[t] = Qy.any ? v : 0.0f;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // before the next batch overwrites
     }
 }
 
@@ -692,7 +906,12 @@ extern "C" int sdmm_product_pdf(const float* table, int32_t n_cells, int32_t K, 
     if (!qpos || !qcell || !bpar || !bcell || !frames || !dirs || !pdf_out) return SDMM_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K > Kb ? K : Kb);
-    SDMM_DISPATCH_G(G, (product_pdf_kernel<g><<<grid_for(nq, 64 / g), 256, 0, s>>>(
+    if (nq >= kStagedCall)
+        SDMM_DISPATCH_G(G, (product_pdf_staged_kernel<g><<<grid_for(nq, kStagedQueries), 256, 0, s>>>(
+                               table, n_cells, K, qpos, qcell, btable, n_bsdf, Kb, bpar, bcell, frames, nq, nd, dirs,
+                               pdf_out)))
+    else
+        SDMM_DISPATCH_G(G, (product_pdf_kernel<g><<<grid_for(nq, 64 / g), 256, 0, s>>>(
                            table, n_cells, K, qpos, qcell, btable, n_bsdf, Kb, bpar, bcell, frames, nq, nd, dirs,
                            pdf_out)));
     return check(hipGetLastError());

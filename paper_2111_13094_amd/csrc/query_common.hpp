@@ -196,7 +196,9 @@ __device__ __forceinline__ float cond_log_weight(float lw, float& w)
 __device__ __forceinline__ const float* table_row(const float* table, int qc, int K, int comp, bool usable)
 {
     const int kk = comp < K ? comp : K - 1;
-    return table + (int64_t)(usable ? qc : 0) * K * kCond + (int64_t)kk * 4;
+    // one 32 x 32 -> 64-bit product (a usable cell index is not negative)
+    const uint64_t cell = (uint64_t)(uint32_t)(usable ? qc : 0) * (uint32_t)(K * kCond * (int)sizeof(float));
+    return reinterpret_cast<const float*>(reinterpret_cast<const char*>(table + kk * 4) + cell);
 }
 
 // the kCond floats of one component, chunk q at q * K chunks from the first

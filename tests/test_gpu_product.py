@@ -253,3 +253,43 @@ def test_product_full_size_sampled_queries(dev, orc):
     u = u_all.reshape(nq, ns, 3)[pick].astype(np.float32)
     amb = _compare(orc, sub, u, (gd[pick], gp[pick], gv[pick], gpair[pick]), {})
     assert amb <= 2, amb
+
+
+@pytest.mark.parametrize("K,Kb", [(16, 16), (4, 3), (7, 5), (32, 20), (64, 2)])
+@pytest.mark.parametrize("nq", [131072, 131101])
+def test_large_product_calls_equal_their_parts(dev, K, Kb, nq):
+    """Calls whose pdf shares the rotation of the kept BSDF components among the 32 queries of
+    a wave pass (the size where that begins, and one with a ragged last pass), on queries in arbitrary order with indices out of range, against the same queries
+    in parts too small for it. The draws are bitwise equal. So are a part's and the whole's
+    pdf inputs; the compiler may contract the two forms differently, which moves a pair's
+    covariance and quadratic form by a few FP32 roundings (relative 1e-6 times cond(S), up to
+    1e2): the tolerance against the oracle holds between them too, 2e-6 for values near 0."""
+    print("case: large product calls", K, Kb, nq, flush=True)
+    from paper_2111_13094_amd import sdmm
+    C, CB, ns, nd = 12, 2, 2, 1
+    rng = np.random.default_rng(K + nq)
+    lo = rng.random((C, 3))
+    mix = synth.initial_mixtures(lo, np.full((C, 3), 0.3), K)
+    qcell = rng.integers(0, C, nq).astype(np.int32)
+    qpos = (lo[qcell] + 0.3 * rng.random((nq, 3))).astype(np.float32)
+    bpar, bcell, F = synth.bsdf_queries(5, nq, CB)
+    qcell[rng.integers(0, nq, 5)] = C
+    bcell[rng.integers(0, nq, 5)] = -1
+    sc = dict(C=C, K=K, mix=mix, CB=CB, Kb=Kb, bmix=synth.bsdf_mixtures(6, CB, Kb), qpos=qpos, qcell=qcell,
+              bpar=bpar.astype(np.float32), bcell=bcell, F=F.astype(np.float32))
+    g = _gpu_inputs(dev, sc)
+    u = dev.from_numpy(np.ascontiguousarray(synth.make_uniforms(3, nq * ns).T)).cuda()
+    d = rng.normal(size=(nq * nd, 3))
+    d = dev.from_numpy(np.ascontiguousarray((d / np.linalg.norm(d, axis=1, keepdims=True)).T.astype(np.float32))).cuda()
+
+    def call(a, b):
+        q = [g[k][..., a:b].contiguous() for k in ("qpos", "qcell", "bpar", "bcell", "frames")]
+        args = (g["table"], C, K, q[0], q[1], g["btable"], CB, Kb, q[2], q[3], q[4])
+        return (*sdmm.product_sample(*args, ns, uniforms=u[:, a * ns:b * ns].contiguous())[:3],
+                sdmm.product_pdf(*args, d[:, a * nd:b * nd].contiguous()))
+
+    whole = call(0, nq)
+    parts = [call(a, min(nq, a + 9973)) for a in range(0, nq, 9973)]
+    for j, axis in enumerate((1, 0, 0)):
+        assert dev.equal(whole[j], dev.cat([p[j] for p in parts], dim=axis)), j
+    dev.testing.assert_close(whole[3], dev.cat([p[3] for p in parts]), rtol=PDF_RTOL, atol=2e-6)
