@@ -259,8 +259,9 @@ def test_product_full_size_sampled_queries(dev, orc):
 @pytest.mark.parametrize("nq", [131072, 131101])
 def test_large_product_calls_equal_their_parts(dev, K, Kb, nq):
     """Calls whose pdf shares the rotation of the kept BSDF components among the 32 queries of
-    a wave pass (the size where that begins, and one with a ragged last pass), on queries in arbitrary order with indices out of range, against the same queries
-    in parts too small for it. The draws are bitwise equal. So are a part's and the whole's
+    a wave pass (the size where that begins, and one with a ragged last pass), on queries in
+    arbitrary order with indices out of range, against the same queries in parts too small
+    for it. The draws are bitwise equal. So are a part's and the whole's
     pdf inputs; the compiler may contract the two forms differently, which moves a pair's
     covariance and quadratic form by a few FP32 roundings (relative 1e-6 times cond(S), up to
     1e2): the tolerance against the oracle holds between them too, 2e-6 for values near 0."""
