@@ -330,3 +330,36 @@ def test_adjoint_at_the_4096_cell_state_after_8_batches(dev, orc):
     assert worst["g64"] < 1e-7 and worst["alpha32"] < 1e-4, worst
     assert worst["mean32"] < 2e-4 and worst["L32"] < 2e-4, worst
     assert worst["fd_orc"] < 1e-6 and worst["fd_gpu"] < 1e-6, worst
+
+
+@pytest.mark.parametrize("K", [3, 7, 16, 20, 40])
+def test_cells_of_one_work_group_equal_each_alone(dev, K):
+    """The assembly takes 64 / G cells per work group (G = K rounded up to a power of two):
+    five cells, one of them empty and one below the sample minimum, leave the last group
+    partly filled for every G but 64. Each cell's outputs are bitwise those of the cell
+    alone, since no value of a cell depends on its neighbours."""
+    print("case: adjoint, cells of one work group, K", K, flush=True)
+    from paper_2111_13094_amd import sdmm
+    rng = np.random.default_rng(K)
+    counts = [600, 0, 300, 5, 257]
+    C = len(counts)
+    lo = rng.random((C, 3))
+    b = synth.make_batch(9, counts, lo, np.full((C, 3), 0.3), synth.planted_lobes(5))
+    mix = synth.initial_mixtures(lo, np.full((C, 3), 0.3), K)
+    mix["pi"] = rng.dirichlet(np.full(K, 2.0), C).reshape(-1)
+    o = sdmm.default_opts(K, prior_mode=sdmm.PRIOR_FIXED, prior_scale=0.02)
+    smp = dev.from_numpy(b.samples).cuda()
+
+    def grad(off, a, z):
+        part = {k: v.reshape(C, -1)[a:z].reshape(-1) for k, v in mix.items()}
+        i, j = int(b.offsets[a]), int(b.offsets[z])
+        return sdmm.fit_grad(dev.from_numpy(off).cuda(), smp[:, i:j].contiguous(), to_torch(part), o)
+
+    whole = grad(b.offsets, 0, C)
+    assert whole["status"].cpu().tolist()[1] != 0 and whole["status"].cpu().tolist()[0] == 0
+    for c in range(C):
+        if counts[c] == 0:
+            continue
+        alone = grad(np.array([0, counts[c]], dtype=np.int64), c, c + 1)
+        for key, v in alone.items():
+            assert dev.equal(v[0], whole[key][c]), (c, key)
