@@ -1,0 +1,39 @@
+// launch_rules.hpp -- the rules that choose a kernel or cut its work from a call's sizes, in
+// plain C++ (no HIP), so that they can be checked over the whole range of the sizes that the
+// entry points accept. Sizes are valid arguments: S = 64 / G queries side by side in a wave
+// (G component lanes each, a power of two from 4 to 64), ns >= 1 draws per query.
+#pragma once
+
+#include <cstdint>
+
+namespace sdmm {
+
+// Whether the draws of a wave's S queries fit its 64 lanes, one draw each (the lanes
+// kernels' phase B). ns has no upper limit, so ns * S may not fit 32 bits.
+constexpr bool lanes_fit(int S, int ns) { return ns <= 64 / S; }
+
+// rounds of S queries whose draws share one pass of the 64 lanes, at most `most`; for calls
+// that lanes_fit
+constexpr int rounds_per_pass(int S, int ns, int most)
+{
+    const int fit = 64 / (S * ns);
+    return fit < most ? fit : most;
+}
+
+constexpr int kLanesRounds = 4;  // most rounds of S queries per pass of the query kernels
+
+// wave groups below which a query launch keeps one round per wave (four waves per SIMD, so
+// that a small call spreads out)
+constexpr int64_t kFewGroups = 4096;
+
+// rounds of the query kernels' passes: as many as fill the lanes, at most kLanesRounds (more
+// take the LDS of one wave less per SIMD: 4% slower in path order), fewer where the call is
+// too small to give every SIMD four waves of that many
+constexpr int lanes_rounds(int64_t nq, int S, int ns)
+{
+    int nqr = rounds_per_pass(S, ns, kLanesRounds);
+    while (nqr > 1 && nq < kFewGroups * S * nqr) nqr >>= 1;
+    return nqr;
+}
+
+}  // namespace sdmm

@@ -882,9 +882,9 @@ extern "C" int sdmm_product_sample(const float* table, int32_t n_cells, int32_t 
     const int G = group_for(K > Kb ? K : Kb);
     ScopedTimer tm(SDMM_TIMER_PRODUCT, s);
     const int S = 64 / G;
-    if (S * ns <= 64) {
+    if (lanes_fit(S, ns)) {
         // the draws of up to two rounds of S queries share one pass of the draw phase
-        const int nqr = std::max(1, std::min(kProdRounds, 64 / (S * ns)));
+        const int nqr = rounds_per_pass(S, ns, kProdRounds);
         SDMM_DISPATCH_G(G, (product_sample_lanes_kernel<g><<<grid_for(nq, S * nqr, kProdWpb), 64 * kProdWpb, 0, s>>>(
                                table, n_cells, K, qpos, qcell, btable, n_bsdf, Kb, bpar, bcell, frames, nq, ns, nqr,
                                uniforms, seed, dirs_out, pdf_out, valid_out, pair_out)));

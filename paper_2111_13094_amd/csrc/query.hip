@@ -379,8 +379,6 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_kernel(const float* __res
     }
 }
 
-constexpr int kLanesRounds = 4;  // most rounds of S queries per pass
-
 // The same draws and pdf as cond_sample_pdf_kernel and sample_kernel, in three wave-local
 // phases over QB = S * nqr queries, nqr rounds of S queries with QB * ns <= 64 draws:
 //   A. lane = (query slot, component), per round: pi' and m, conditioned here or (Given)
@@ -599,20 +597,7 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(
     }
 }
 
-// rounds per pass of the condition and pdf kernels, and the wave groups below which a launch
-// keeps one round per wave (four waves per SIMD, so that a small call spreads out)
-constexpr int kRounds = 4;
-constexpr int64_t kFewGroups = 4096;
-
-// rounds of S queries that share one pass of the draws: as many as fill its 64 lanes, at
-// most kLanesRounds (more take the LDS of one wave less per SIMD: 4% slower in path order),
-// fewer where the call is too small to give every SIMD four waves of that many
-static int lanes_rounds(int64_t nq, int S, int ns)
-{
-    int nqr = std::max(1, std::min(kLanesRounds, 64 / (S * ns)));
-    while (nqr > 1 && nq < kFewGroups * S * nqr) nqr >>= 1;
-    return nqr;
-}
+constexpr int kRounds = 4;  // rounds per pass of the condition and pdf kernels
 
 }  // namespace sdmm
 
@@ -680,7 +665,7 @@ extern "C" int sdmm_sample(const float* table, int32_t n_cells, int32_t K, const
     // a table that fits one XCD's L2 (4 MB): the lanes kernel, which reads the picked
     // component's row once more per draw; from a larger one and in path order those reads
     // cost more than they save (500009 queries, 8 MB: 79.9 against 61.7 us)
-    if (S * ns <= 64 && (int64_t)n_cells * K * kCond * (int64_t)sizeof(float) <= (4 << 20)) {
+    if (lanes_fit(S, ns) && (int64_t)n_cells * K * kCond * (int64_t)sizeof(float) <= (4 << 20)) {
         const int nqr = lanes_rounds(nq, S, ns);
         SDMM_DISPATCH_G(G, (cond_sample_pdf_lanes_kernel<g, true><<<grid_for(nq, S * nqr), 256, 0, s>>>(
                                table, n_cells, K, nullptr, cond_w, cond_m, qcell, nq, ns, nqr, uniforms, seed, dirs_out,
@@ -705,7 +690,7 @@ extern "C" int sdmm_condition_sample_pdf(const float* table, int32_t n_cells, in
     const int G = group_for(K);
     ScopedTimer tm(SDMM_TIMER_QUERY, s);
     const int S = 64 / G;
-    if (S * ns <= 64) {
+    if (lanes_fit(S, ns)) {
         const int nqr = lanes_rounds(nq, S, ns);
         SDMM_DISPATCH_G(G, (cond_sample_pdf_lanes_kernel<g, false><<<grid_for(nq, S * nqr), 256, 0, s>>>(
                                table, n_cells, K, qpos, nullptr, nullptr, qcell, nq, ns, nqr, uniforms, seed, dirs_out,

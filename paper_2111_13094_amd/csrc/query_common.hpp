@@ -5,6 +5,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "launch_rules.hpp"
 
 namespace sdmm {
 

@@ -282,3 +282,23 @@ def test_fused_path_matches_the_separate_calls(dev, orc, K, ns):
     f1, q1, w1 = sdmm.condition_sample_pdf(table, 1, K, qp, qc, ns, uniforms=None, seed=77)
     assert dev.equal(w1, v1)
     assert np.allclose(f1.cpu().numpy(), d1.cpu().numpy(), rtol=0, atol=1e-6)
+
+
+@pytest.mark.parametrize("K,ns", [(4, (1 << 27) + 3), (16, 1 << 26)])
+def test_very_many_draws_of_one_query(dev, K, ns):
+    """One query with so many draws that their product with the queries of a wave leaves 32
+    bits (K = 4) or comes close to it: the first and the last draws equal, bit for bit, those
+    of calls with only these draws' uniforms."""
+    print("case: one query with", ns, "draws, K", K, flush=True)
+    from paper_2111_13094_amd import sdmm
+    mix = synth.initial_mixtures(np.zeros((1, 3)), np.full((1, 3), 0.3), K)
+    table, qp, qc, cw, cm = _gpu_cond(dev, mix, 1, K, np.full((1, 3), 0.1, dtype=np.float32), np.zeros(1, np.int32))
+    gen = dev.Generator(device="cuda")
+    gen.manual_seed(K)
+    u = dev.rand(3, ns, generator=gen, device="cuda")
+    d, p, v, c = sdmm.sample(table, 1, K, qc, cw, cm, ns, uniforms=u, with_comp=True)
+    for sl in (slice(0, 1000), slice(ns - 1000, ns)):
+        e = sdmm.sample(table, 1, K, qc, cw, cm, 1000, uniforms=u[:, sl].contiguous(), with_comp=True)
+        assert e[2].any()
+        for got, want in ((d[:, sl], e[0]), (p[sl], e[1]), (v[sl], e[2]), (c[sl], e[3])):
+            assert dev.equal(got, want)
