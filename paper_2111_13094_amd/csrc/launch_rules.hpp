@@ -20,6 +20,10 @@ constexpr int rounds_per_pass(int S, int ns, int most)
     return fit < most ? fit : most;
 }
 
+// batches of G draws of a query, the last of what is left (a counter that advances by G
+// would pass 2^31 where ns is within G of it, and never end)
+constexpr int draw_batches(int ns, int G) { return ns / G + (ns % G != 0 ? 1 : 0); }
+
 constexpr int kLanesRounds = 4;  // most rounds of S queries per pass of the query kernels
 
 // wave groups below which a query launch keeps one round per wave (four waves per SIMD, so

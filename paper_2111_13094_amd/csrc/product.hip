@@ -497,10 +497,11 @@ __global__ __launch_bounds__(256) void product_sample_kernel(
         const uint64_t pos = __ballot(cand && s > 0.0f) & gmask;
         const int last_pos = pos ? 63 - __builtin_clzll(pos) - base : -1;
         const int j_last = __shfl(Qy.P1 > 0.0f ? 1 : 0, base + (last_pos < 0 ? 0 : last_pos));
-        for (int t0 = 0; t0 < ns; t0 += G) {
-            float ul0 = 0.0f, ul1 = 0.0f, ul2 = 0.0f;
-            if (t0 + comp < ns) draw_uniforms(uniforms, nd, qq * ns + t0 + comp, seed, ul0, ul1, ul2);
+        for (int batch = 0; batch < draw_batches(ns, G); ++batch) {
+            const int t0 = batch * G;
             const int tn = min(G, ns - t0);  // wave-uniform
+            float ul0 = 0.0f, ul1 = 0.0f, ul2 = 0.0f;
+            if (comp < tn) draw_uniforms(uniforms, nd, qq * ns + t0 + comp, seed, ul0, ul1, ul2);
             // pair of every draw of the batch, four at a time (a draw past tn repeats the
             // last one and is not kept); lane c keeps the one of draw t0 + c
             int sel = -1, j = 0;

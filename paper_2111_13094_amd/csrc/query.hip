@@ -327,10 +327,11 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_kernel(const float* __res
         const bool cand = comp < K && usable;
         const uint64_t pos = __ballot(cand && wk > 0.0f) & gmask;
         const int last_pos = pos ? 63 - __builtin_clzll(pos) - base : -1;
-        for (int t0 = 0; t0 < ns; t0 += G) {
-            float ul0 = 0.0f, ul1 = 0.0f, ul2 = 0.0f;
-            if (t0 + comp < ns) draw_uniforms(uniforms, nd, qq * ns + t0 + comp, seed, ul0, ul1, ul2);
+        for (int batch = 0; batch < draw_batches(ns, G); ++batch) {
+            const int t0 = batch * G;
             const int tn = min(G, ns - t0);  // wave-uniform
+            float ul0 = 0.0f, ul1 = 0.0f, ul2 = 0.0f;
+            if (comp < tn) draw_uniforms(uniforms, nd, qq * ns + t0 + comp, seed, ul0, ul1, ul2);
             // four draws at a time, so that their independent chains interleave (a draw
             // past tn repeats the last one and is not kept)
             int sel = -1;

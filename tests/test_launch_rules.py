@@ -43,6 +43,15 @@ def test_draws_of_a_pass_fit_its_lanes(rules):
         assert b == min(2, 64 // (S * ns)), (S, ns)
 
 
+def test_batches_cover_every_draw(rules):
+    """The batches of G draws cover all ns draws and their first draw's index stays in 32
+    bits, up to the largest ns."""
+    cases = [(G, ns) for G in (4, 8, 16, 32, 64)
+             for ns in (1, G - 1, G, G + 1, 1000, INT32_MAX - G, INT32_MAX - 1, INT32_MAX)]
+    for (G, ns), n in zip(cases, rules([f"draw_batches(v * {ns}, {G})" for G, ns in cases])):
+        assert (n - 1) * G < ns <= n * G, (G, ns)
+
+
 @pytest.mark.parametrize("K,ns", [(4, 1 << 28), (16, 1 << 30), (4, 1 << 27)])
 def test_calls_with_many_draws_reach_the_launch(K, ns):
     """Draw counts whose product with the queries of a wave leaves 32 bits: with no device in
