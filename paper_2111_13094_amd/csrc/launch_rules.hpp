@@ -40,4 +40,28 @@ constexpr int lanes_rounds(int64_t nq, int S, int ns)
     return nqr;
 }
 
+// The chunks (work items) of a leaf of a tree refinement: `count` records, up to 2^31 - 1,
+// in chunks of at most `most` (a multiple of 64), all of one size, a multiple of 64, but the
+// last, which takes what is left. Nothing here may add to a count before it divides: a leaf
+// within a chunk of 2^31 records would leave 32 bits.
+constexpr int32_t chunks_of(int32_t count, int32_t most) { return count / most + (count % most != 0 ? 1 : 0); }
+
+constexpr int32_t chunk_size(int32_t count, int32_t n_chunks)
+{
+    return (count / n_chunks + (count % n_chunks != 0 ? 1 : 0) + 63) & ~63;
+}
+
+// records [begin, end) of chunk q < n_chunks = chunks_of(count, most)
+constexpr int32_t chunk_begin(int32_t count, int32_t n_chunks, int32_t q)
+{
+    const int32_t at = q * chunk_size(count, n_chunks);
+    return at < count ? at : count;
+}
+
+constexpr int32_t chunk_end(int32_t count, int32_t n_chunks, int32_t q)
+{
+    const int32_t begin = chunk_begin(count, n_chunks, q), size = chunk_size(count, n_chunks);
+    return count - begin < size ? count : begin + size;
+}
+
 }  // namespace sdmm

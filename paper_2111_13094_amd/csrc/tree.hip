@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "launch_rules.hpp"
 #include "timing.hpp"
 
 namespace sdmm {
@@ -436,8 +437,6 @@ struct RoundBufs {
     int32_t max_items;
 };
 
-__device__ __forceinline__ int32_t chunks_of(int32_t count) { return (count + kChunk - 1) / kChunk; }
-
 // One work group: a pass's bins get their bases (exclusive prefix sum of the totals); with
 // leaves, every bin is a leaf and the leaf tables are set from them (else from the starts
 // that starts_kernel wrote), and the first round's list takes every leaf with more than c
@@ -478,7 +477,7 @@ __global__ __launch_bounds__(1024) void base_kernel(int32_t* __restrict__ total,
             lt.origin[l] = l;
         }
         const bool in = n > c;
-        const int32_t nch = in ? chunks_of(n) : 0;
+        const int32_t nch = in ? chunks_of(n, kChunk) : 0;
         int64_t all;
         const int64_t x = block_scan_1024(((int64_t)(in ? 1 : 0) << 32) | nch, ws, all);
         if (in) {
@@ -707,9 +706,8 @@ __global__ __launch_bounds__(kSortThreads) void scatter_kernel(
 // ---------------------------------------------------------------------------------
 __device__ __forceinline__ void chunk_range(const Entry& e, int32_t q, int32_t& lo, int32_t& hi)
 {
-    const int32_t cs = ((e.count + e.nch - 1) / e.nch + 63) & ~63;
-    lo = min(e.count, q * cs);
-    hi = min(e.count, lo + cs);
+    lo = chunk_begin(e.count, e.nch, q);
+    hi = chunk_end(e.count, e.nch, q);
 }
 
 // a thread's running statistics
@@ -1059,8 +1057,8 @@ __global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, RoundBuf
                 }
             }
             const int32_t nl = e.count - nr;
-            auto left = [&](bool go) { return go && nl > c ? (int64_t(1) << 32) | chunks_of(nl) : int64_t(0); };
-            auto right = [&](bool go) { return go && nr > c ? (int64_t(1) << 32) | chunks_of(nr) : int64_t(0); };
+            auto left = [&](bool go) { return go && nl > c ? (int64_t(1) << 32) | chunks_of(nl, kChunk) : int64_t(0); };
+            auto right = [&](bool go) { return go && nr > c ? (int64_t(1) << 32) | chunks_of(nr, kChunk) : int64_t(0); };
             int64_t a = left(want) | ((int64_t)want << kWantShift), b = right(want), a_all, b_all;
             scan2(a, b, a_all, b_all);
             const int32_t rk = total + (int32_t)(a >> kWantShift), wants = (int32_t)(a_all >> kWantShift);
@@ -1113,7 +1111,7 @@ __global__ __launch_bounds__(1024) void split_decide_kernel(TreePtrs t, RoundBuf
             for (int side = 0; side < 2; ++side) {
                 if (!(side ? rgo : lgo)) continue;
                 const int64_t at = side ? b : a;
-                const int32_t en = (int32_t)(at >> 32), it = (int32_t)at, cnt = side ? nr : nl, nch = chunks_of(cnt);
+                const int32_t en = (int32_t)(at >> 32), it = (int32_t)at, cnt = side ? nr : nl, nch = chunks_of(cnt, kChunk);
                 rb.entries[par ^ 1][en] = Entry{side ? r : l, side ? e.start + nl : e.start, cnt, e.src ^ 1, it, nch,
                                                 e.item0, 2 * e.nch + side};
                 rb.rtot[par ^ 1][en] = 0;

@@ -52,6 +52,23 @@ def test_batches_cover_every_draw(rules):
         assert (n - 1) * G < ns <= n * G, (G, ns)
 
 
+def test_chunks_of_a_leaf_cover_it_once(rules):
+    """A leaf's chunks of at most 4096 records follow each other, cover all its records and
+    hold at most 4096 each, up to the largest leaf that a refinement accepts."""
+    most = 4096
+    counts = [1, 63, 64, 4095, 4096, 4097, 8192, 8193, 200003, 16616003, INT32_MAX - most, INT32_MAX - most + 1,
+              INT32_MAX - 1, INT32_MAX]
+    n_chunks = rules([f"chunks_of(v * {c}, {most})" for c in counts])
+    assert n_chunks == [-(-c // most) for c in counts]
+    pick = [(c, n, q) for c, n in zip(counts, n_chunks) for q in sorted({0, 1, n // 2, n - 2, n - 1}) if 0 <= q < n]
+    begin = rules([f"chunk_begin(v * {c}, {n}, {q})" for c, n, q in pick])
+    end = rules([f"chunk_end(v * {c}, {n}, {q})" for c, n, q in pick])
+    for (c, n, q), lo, hi in zip(pick, begin, end):
+        size = (-(-c // n) + 63) // 64 * 64
+        assert (lo, hi) == (min(c, q * size), min(c, (q + 1) * size)) and hi - lo <= most, (c, n, q)
+        assert (q > 0 or lo == 0) and (q < n - 1 or hi == c), (c, n, q)
+
+
 @pytest.mark.parametrize("K,ns", [(4, 1 << 28), (16, 1 << 30), (4, 1 << 27)])
 def test_calls_with_many_draws_reach_the_launch(K, ns):
     """Draw counts whose product with the queries of a wave leaves 32 bits: with no device in
