@@ -293,3 +293,54 @@ def test_full_size_refinement(dev, orc):
     pick = np.random.default_rng(2).choice(smp.shape[1], 1 << 20, replace=False)
     assert np.array_equal(srt_g[:, dev.from_numpy(pick).cuda()].cpu().numpy(), srt_o[:, pick])
     print("leaves", L, "nodes", t_orc.n_nodes)
+
+
+def _clustered(n, seed):
+    """Samples about three points of the box, so that a fine tree's other leaves are empty."""
+    smp = _samples(n, seed)
+    rng = np.random.default_rng(seed)
+    centre = np.array([[0.03, 0.02, 0.04], [0.96, 0.97, 0.95], [0.52, 0.13, 0.91]])[rng.integers(0, 3, n)]
+    smp[3:6] = np.clip(centre + 0.01 * rng.normal(size=(n, 3)), 0, 1).T
+    return smp
+
+
+@pytest.mark.parametrize("n,depth,c", [
+    (700, 3, 100),      # fewer and more leaves to follow than a search takes over from
+    (1000, 4, 1 << 30),  # no leaf splits
+    (1, 4, 1),          # one sample among 4096 leaves
+    (20001, 5, 300),    # 32768 leaves (two sorting passes), the full ones split
+])
+def test_refine_with_runs_of_empty_leaves(dev, orc, n, depth, c):
+    """Records that lie next to each other but whose leaves are thousands of indices apart."""
+    print("case: clustered samples", n, depth, c, flush=True)
+    L0 = 8 ** depth
+    t_gpu, t_orc, g, o = _refine_both(dev, orc, _clustered(n, 31), c, L0 + 1024, depth=depth, seed=32, n_init=3)
+    assert (np.diff(o[1]) == 0).sum() > L0 // 2
+    _assert_refine_equal(t_gpu, t_orc, g, o)
+
+
+def test_refine_time_does_not_follow_the_empty_leaves(dev):
+    """1000 samples in a tree of 262144 leaves, nearly all empty: about 2 ms, 47 ms when the
+    last kernel stepped through the empty leaves one by one."""
+    print("case: 1000 samples, 262144 leaves", flush=True)
+    from paper_2111_13094_amd import sdmm
+    L0 = 8 ** 6
+    t = sdmm.new_tree(L0)
+    sdmm.tree_init(t, 6, [0, 0, 0], [1, 1, 1])
+    mix = {k: dev.zeros(L0 * n, dtype=dev.float64, device="cuda") for k, n in
+           (("pi", 1), ("mu_dir", 3), ("mu_pos", 3), ("cov", 15))}
+    st = sdmm.new_state(L0, 1)
+    smp = _samples(1000, 33)
+    smp[3:6] **= 3
+    smp = dev.from_numpy(smp).cuda()
+    times = []
+    for _ in range(4):
+        a, b = dev.cuda.Event(enable_timing=True), dev.cuda.Event(enable_timing=True)
+        a.record()
+        srt, off, L, status = sdmm.tree_refine(t, smp, 1 << 30, mix, st, 1)
+        b.record()
+        dev.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    assert L == L0 and status == 0 and int(off[-1]) == 1000
+    assert dev.equal(srt.sort(dim=1)[0], smp.sort(dim=1)[0])
+    assert min(times) < 15.0, times
