@@ -1462,6 +1462,9 @@ extern "C" int sdmm_tree_refine(const sdmm_tree* tree, const float* samples, int
     const int32_t L0 = pinned[1];
     if (L0 < 1 || L0 > tree->max_leaves || pinned[0] < 1 || pinned[0] > tree->max_nodes) return SDMM_EINVAL;
 
+    // one leaf that will not split keeps its samples as they are, and their order: the output
+    // is a copy (8M samples: 310 us through the records and the gather)
+    const bool as_is = L0 == 1 && N <= split_threshold;
     // the stable sort by leaf: one pass up to kMaxBins leaves, which leaves the leaf tables
     // and the first round's list behind; more leaves take more passes
     int passes = 1;
@@ -1482,8 +1485,9 @@ extern "C" int sdmm_tree_refine(const sdmm_tree* tree, const float* samples, int
         const size_t lds = staged ? 0 : (size_t)bins * (4 + 2 * kSortWaves);
         const auto move = p == 0 ? (staged ? scatter_kernel<true, true> : scatter_kernel<true, false>)
                                  : (staged ? scatter_kernel<false, true> : scatter_kernel<false, false>);
-        move<<<TL.tiles, kSortThreads, lds, s>>>(samples, f4(TL.p[to ^ 1]), f4(TL.q[to ^ 1]), kin, N, shift, bins, bits, hist,
-                                                 gsum, bin_total, f4(TL.p[to]), f4(TL.q[to]), kout);
+        if (!as_is)
+            move<<<TL.tiles, kSortThreads, lds, s>>>(samples, f4(TL.p[to ^ 1]), f4(TL.q[to ^ 1]), kin, N, shift, bins, bits,
+                                                     hist, gsum, bin_total, f4(TL.p[to]), f4(TL.q[to]), kout);
     }
     if (passes > 1 || N == 0) {
         if (N > 0)
@@ -1514,9 +1518,14 @@ extern "C" int sdmm_tree_refine(const sdmm_tree* tree, const float* samples, int
         const int done = round >= kMaxRounds ? 2 : round & 1;
         offsets_kernel<<<1, 1024, 0, s>>>(ctl, done, lt, cell_offsets_out);
         copy_leaves_kernel<<<std::min(tree->max_leaves, 2048), 64, 0, s>>>(L0, ctl, done, lt, K, mp, sp);
-        if (N > 0)
+        if (as_is) {
+            if (N > 0 && (rc = check(hipMemcpyAsync(sorted_out, samples, (size_t)N * 7 * sizeof(float),
+                                                    hipMemcpyDeviceToDevice, s))))
+                return rc;
+        } else if (N > 0) {
             gather_kernel<<<blocks_for(N, 4 * kCover), 256, 0, s>>>(ctl, done, N, L0, lt, cell_offsets_out, P0, P1,
                                                                     f4(TL.q[0]), sorted_out);
+        }
         init_leaves_kernel<<<std::min(tree->max_leaves, 4096), 64, 0, s>>>(tp, ctl, done, cell_offsets_out, min_init, K,
                                                                            mp, sp);
         if ((rc = read_back(ctl, kCtlWords))) return rc;

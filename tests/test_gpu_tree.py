@@ -344,3 +344,12 @@ def test_refine_time_does_not_follow_the_empty_leaves(dev):
     assert L == L0 and status == 0 and int(off[-1]) == 1000
     assert dev.equal(srt.sort(dim=1)[0], smp.sort(dim=1)[0])
     assert min(times) < 15.0, times
+
+
+@pytest.mark.parametrize("n,c", [(1, 1), (4097, 4097), (4097, 4096), (70001, 1 << 30)])
+def test_refine_of_one_leaf(dev, orc, n, c):
+    """One leaf with at most c samples, which stay as they are, and with one more."""
+    print("case: one leaf", n, c, flush=True)
+    t_gpu, t_orc, g, o = _refine_both(dev, orc, _samples(n, 41), c, 4, depth=0, seed=42, n_init=1)
+    assert (t_orc.n_leaves == 1) == (n <= c)
+    _assert_refine_equal(t_gpu, t_orc, g, o)
