@@ -20,6 +20,19 @@ constexpr int rounds_per_pass(int S, int ns, int most)
     return fit < most ? fit : most;
 }
 
+// Whether separate draws (conditioned before) run on the lanes kernel. It scans a query's
+// CDF once for its draws and draws on all lanes, but reads the picked component's row once
+// more per draw. With two draws or more that pays from a table that fits one XCD's L2
+// (4 MB): 400,000 queries of 16 components in random order, 2 draws 48-53 us, 79-80 by the
+// group kernel, 4 draws 56-59 and 152. With one draw it costs up to a third in random
+// order (1M queries of 4 components 48.0 against 35.9 us, of 32 288 and 231) and gives 13%
+// at most in the order of the cells, which the host doesn't know. From a larger table those
+// reads leave the L2 (500,009 queries of one draw, 8 MB: 79.9 against 61.7 us).
+constexpr bool sample_by_lanes(int S, int ns, int64_t table_bytes)
+{
+    return ns >= 2 && lanes_fit(S, ns) && table_bytes <= (4 << 20);
+}
+
 // batches of G draws of a query, the last of what is left (a counter that advances by G
 // would pass 2^31 where ns is within G of it, and never end)
 constexpr int draw_batches(int ns, int G) { return ns / G + (ns % G != 0 ? 1 : 0); }

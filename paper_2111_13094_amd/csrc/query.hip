@@ -663,10 +663,7 @@ extern "C" int sdmm_sample(const float* table, int32_t n_cells, int32_t K, const
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K);
     const int S = 64 / G;
-    // a table that fits one XCD's L2 (4 MB): the lanes kernel, which reads the picked
-    // component's row once more per draw; from a larger one and in path order those reads
-    // cost more than they save (500009 queries, 8 MB: 79.9 against 61.7 us)
-    if (lanes_fit(S, ns) && (int64_t)n_cells * K * kCond * (int64_t)sizeof(float) <= (4 << 20)) {
+    if (sample_by_lanes(S, ns, (int64_t)n_cells * K * kCond * (int64_t)sizeof(float))) {
         const int nqr = lanes_rounds(nq, S, ns);
         SDMM_DISPATCH_G(G, (cond_sample_pdf_lanes_kernel<g, true><<<grid_for(nq, S * nqr), 256, 0, s>>>(
                                table, n_cells, K, nullptr, cond_w, cond_m, qcell, nq, ns, nqr, uniforms, seed, dirs_out,

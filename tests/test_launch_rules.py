@@ -43,6 +43,15 @@ def test_draws_of_a_pass_fit_its_lanes(rules):
         assert b == min(2, 64 // (S * ns)), (S, ns)
 
 
+def test_one_separate_draw_keeps_the_group_kernel(rules):
+    """Separate draws take the lanes kernel from two draws up, while they fit the lanes and
+    the table fits one L2."""
+    cases = [(S, ns, t) for S in (1, 4, 16) for ns in (1, 2, 4, 64 // S, 64 // S + 1, INT32_MAX)
+             for t in (128, 4 << 20, (4 << 20) + 128, 1 << 40)]
+    got = rules([f"sample_by_lanes({S}, v * {ns}, {t}LL)" for S, ns, t in cases])
+    assert got == [int(2 <= ns and S * ns <= 64 and t <= 4 << 20) for S, ns, t in cases]
+
+
 def test_batches_cover_every_draw(rules):
     """The batches of G draws cover all ns draws and their first draw's index stays in 32
     bits, up to the largest ns."""
