@@ -528,6 +528,12 @@ __global__ __launch_bounds__(64 * (64 / G), G <= 16 ? 4 : 1) void mstep_packed_k
 // blocks' sums in order, and one wave updates. Summed by one wave, 64 records are 11 round
 // trips to memory one after the other: 15.8 us for one cell of 16384 samples, 9.3 us so.
 constexpr int kWideBlocks = kTreeTop / kSumBlock;
+// A cell of one block needs one wave and no barrier. Per iteration (20-iteration fits without
+// max_cell_samples, us, packed / wide): 64 cells of 16 components with 3000 samples each, 12
+// records, 33.4 / 34.5; 20 records 37.3 / 36.9; 39 records 49.3 / 46.0; 78 records 69.8 / 61.5;
+// 256 cells 51.7 / 52.5, 61.8 / 61.0, 102 / 99 and 181 / 174. Small cells lose up to 1.2 us
+// where no bound tells them apart from one large cell among small ones, which the wide form
+// is for (one of 300,000 samples among 256: 55 us where the packed form took 74).
 constexpr int kWideCells = 256;  // most cells of a launch
 
 template <int G, typename RT>
@@ -550,34 +556,39 @@ __global__ __launch_bounds__(64 * kWideBlocks) void mstep_wide_kernel(
     const int lv = *global_ok ? tree_levels_done(global_ok) : 0;
     const int64_t n = records_left(have ? n_items : 0, kTreeLog2R * lv), step = (int64_t)PS << (kTreeLog2R * lv);
     const RT* r0 = static_cast<const RT*>(records) + first * PS;
-    double tot[NT];
+    auto sum_block = [&](int64_t j, int to) {  // block j of the cell's records into blk[to]
+        double v[NQ];
+        sum_block_columns<NCOL, sum_in_flight<NCOL, 4, RT>()>(r0 + j * step, step, (int)min(n - j, (int64_t)kSumBlock), v);
 #pragma unroll
-    for (int i = 0; i < NT; ++i) tot[i] = 0.0;
-    for (int64_t j0 = 0; j0 < n; j0 += kWideBlocks * kSumBlock) {  // once, unless the caller's bound was too low
-        const int64_t j = j0 + w * kSumBlock;
-        if (j < n) {
-            double v[NQ];
-            sum_block_columns<NCOL, sum_in_flight<NCOL, 4, RT>()>(r0 + j * step, step,
-                                                                  (int)min(n - j, (int64_t)kSumBlock), v);
+        for (int q = 0; q < NQ; ++q)
+            if (q * 64 + lane < NCOL) blk[to][q * 64 + lane] = v[q];
+    };
+    if (n <= kSumBlock) {  // one block: its wave needs no other
+        if (w != 0) return;
+        sum_block(0, 0);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // this wave's LDS writes are done
+    } else {
+        double tot[NT];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                if (q * 64 + lane < NCOL) blk[w][q * 64 + lane] = v[q];
+        for (int i = 0; i < NT; ++i) tot[i] = 0.0;
+        for (int64_t j0 = 0; j0 < n; j0 += kWideBlocks * kSumBlock) {  // once, unless the caller's bound was too low
+            if (j0 + w * kSumBlock < n) sum_block(j0 + w * kSumBlock, w);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int col = i * T + (int)threadIdx.x;
+                if (col >= NCOL) continue;
+                for (int b = 0; b < kWideBlocks && j0 + b * kSumBlock < n; ++b) tot[i] += blk[b][col];
+            }
+            __syncthreads();
         }
-        __syncthreads();
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             const int col = i * T + (int)threadIdx.x;
-            if (col >= NCOL) continue;
-            for (int b = 0; b < kWideBlocks && j0 + b * kSumBlock < n; ++b) tot[i] += blk[b][col];
+            if (col < NCOL) blk[0][col] = tot[i];
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        const int col = i * T + (int)threadIdx.x;
-        if (col < NCOL) blk[0][col] = tot[i];
-    }
-    __syncthreads();
     if (w != 0) return;
     const int k = lane % G;
     double S[kStats], X[3];

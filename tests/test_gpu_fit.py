@@ -176,6 +176,57 @@ def test_few_work_items_give_bitwise_the_results_of_many(dev, orc, K, opt):
             assert np.array_equal(a[k].reshape(c1, -1), c[k].reshape(c2, -1)[:n], equal_nan=True), k
 
 
+def _cells_beside(dev, orc, counts, others, K, **opt):
+    """The cells `counts` fitted in a batch of their own and in one with the cells `others`
+    behind them: [(mixtures, state)] with the cells of `counts` only, as [cell, values]."""
+    every = np.array(list(counts) + list(others))
+    rng = np.random.default_rng(7)
+    lo, size = rng.random((every.size, 3)), np.full((every.size, 3), 0.1)
+    b = synth.make_batch(18, every, lo, size, synth.planted_lobes(5))
+    mix0 = synth.initial_mixtures(lo, size, K)
+    n, total = len(counts), int(sum(counts))
+    own = synth.Batch(np.ascontiguousarray(b.samples[:, :total]), b.offsets[:n + 1].copy(), b.lobe)
+    out = []
+    for batch, C in ((own, n), (b, every.size)):
+        gm = to_torch({k: v.reshape(every.size, -1)[:C].reshape(-1).copy() for k, v in mix0.items()})
+        gst = state_to_torch(orc.new_state(C, K))
+        s = _gpu_fit(dev, batch, gm, gst, K=K, **opt)
+        out.append([{k: v.reshape(C, -1)[:n] for k, v in d.items()} for d in (to_numpy(gm), to_numpy(gst))])
+        assert not s[:n][np.array(counts) >= 256].any()
+    return out
+
+
+@pytest.mark.parametrize("K,opt", [(3, {}), (16, {}), (16, {"flags": 4}), (40, {})])
+def test_cells_of_several_record_blocks_give_bitwise_the_packed_sums(dev, orc, K, opt):
+    """Cells of no, one, 15, 16, 17, 32, 33 and 128 records, which no record tree sums first:
+    few cells (one work group per cell, a wave per block of 16 records) against the same cells
+    beside 300 small ones (packed M-steps, one wave per cell)."""
+    print("case: record blocks", K, opt, flush=True)
+    counts = [0, 200, 15 * 256, 16 * 256, 16 * 256 + 1, 32 * 256 - 5, 33 * 256, 128 * 256]
+    few, many = _cells_beside(dev, orc, counts, [20] * 300, K, iters=2, **opt)
+    for a, c in zip(few, many):
+        for k in a:
+            assert np.array_equal(a[k], c[k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("flags", [0, 4])
+def test_cells_beside_one_that_needs_the_record_tree(dev, orc, flags):
+    """Cells of 17 to 128 records beside one of more than 128, for which every cell's blocks
+    of 16 records are summed into their first record. With FP64 records these sums are the
+    ones the M-step forms itself, bit for bit. FP32 records round each block's sum once
+    (2^-24 relative): the statistics of weight, sums of positive terms, differ by at most that."""
+    print("case: record tree beside smaller cells, flags", flags, flush=True)
+    counts = [200, 17 * 256, 40 * 256 + 3, 128 * 256]
+    own, beside = _cells_beside(dev, orc, counts, [129 * 256], 16, iters=1, flags=flags)
+    if flags == 4:
+        for a, c in zip(own, beside):
+            for k in a:
+                assert np.array_equal(a[k], c[k], equal_nan=True), k
+    for k in ("s0", "sw"):
+        assert np.allclose(own[1][k], beside[1][k], rtol=2.0 ** -24 * (1 + 1e-6), atol=0), k
+        assert np.array_equal(own[1][k][0], beside[1][k][0]), k  # one record: nothing to round
+
+
 def test_graph_replays_match_eager(dev, orc):
     print("case: repeated graph replays vs eager", flush=True)
     wl = synth.workload("cells4k", scale=27 / 4096)
