@@ -909,7 +909,10 @@ __device__ __forceinline__ int tree_levels_done(const int32_t* __restrict__ cont
 
 // the level-`level` leader in level slot t, if any, sums its block (see tree_kernel), the
 // block's loads in flight together: one by one they took a level of a 2^24-sample cell
-// 13.4 us in the median, 7.9 us so
+// 13.4 us in the median, 7.9 us so. Of a record of 64 components (22 columns per lane) two
+// are in flight: one by one the leaders of 256 cells of 157 records took 54 us, with one
+// clamped record at a time 82, two 44, four 116 (FP32; FP64 records of the adjoint 108,
+// 145, 103 and 100).
 template <int G, int NS, int NX, typename RT>
 __device__ __forceinline__ void tree_leader(const int64_t* __restrict__ off, int64_t N, int C, int ps, int level,
                                             int64_t t, RT* __restrict__ records, int PS)
@@ -929,7 +932,7 @@ __device__ __forceinline__ void tree_leader(const int64_t* __restrict__ off, int
     const int lane = threadIdx.x & 63;
     RT* r0 = records + (first + base) * PS;
     double v[NQ];
-    sum_block_columns<NCOL, (NQ > 12 ? 4 : 8)>(r0, (int64_t)PS * sub, (int)count, v);
+    sum_block_columns<NCOL, (NQ > 12 ? 2 : 8)>(r0, (int64_t)PS * sub, (int)count, v);
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
         if (q * 64 + lane < NCOL) r0[q * 64 + lane] = (RT)v[q];
