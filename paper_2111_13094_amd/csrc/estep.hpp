@@ -83,7 +83,11 @@ using RecordT = typename std::conditional<(ACC == kAccFp64 || ADJ), double, floa
 
 // A cell's records are summed in blocks of kSumBlock: the records of a block in item order,
 // then the blocks' sums in order. Every kernel that sums records keeps this order (one
-// wave per cell, one wave per block, the record tree), so all give bitwise the same sums.
+// wave per cell, one wave per block, the record tree), so for the same levels of the tree
+// all give bitwise the same sums. The tree leaves a block's sum in the block's first record,
+// in the record's element type: with FP64 records a level changes no bit of the result, with
+// FP32 records it rounds every block's sum (2^-24 relative), so that a cell of more than one
+// block depends, by that rounding, on whether the largest cell of its batch needs a level.
 constexpr int kSumBlock = 16;
 
 // Sums the n <= kSumBlock records of a block, `step` elements apart from r0, one column per

@@ -206,10 +206,13 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t group, int wpb, int wave, in
 // ---------------------------------------------------------------------------------
 // E-step: one wave per work item (see wave_item), slots by the XCD-aware map
 // ---------------------------------------------------------------------------------
-// Most record slots of a launch that the wide E-step takes. Per iteration of one cell (E-step
-// and M-step, us, one-wave / wide pass): 64 items 27.9 / 20.1, 256 items 33.4 / 27.7, 512
-// 33.9 / 32.3, 1024 38.5 / 40.0 with 16 components; 256 items 57.3 / 46.9, 512 58.8 / 59.7
-// with 32; 256 25.3 / 22.9, 512 25.8 / 26.0 with 8.
+// Most record slots of a launch that the wide E-step takes. Per iteration of one cell (E-step,
+// M-step and record tree, us, one-wave / wide pass) at 64, 256, 320 and 512 slots: 4
+// components 16.4 / 15.2, 20.0 / 18.8, 20.7 / 20.5, 20.8 / 20.6; 8: 19.7 / 15.9, 22.9 / 19.9,
+// 24.5 / 22.1, 24.5 / 22.1; 16: 27.0 / 18.6, 30.5 / 22.2, 32.7 / 26.5, 32.9 / 27.0; 32: 46.9 /
+// 26.7, 53.1 / 33.0, 58.2 / 46.5, 57.5 / 45.4; 64: 92 / 41, 115 / 63, 119 / 74, 107 / 62. With
+// 1024 samples an item the wide pass takes 0.46 to 0.80 of the time at 512. Past two groups
+// per CU it no longer gains for every G: 1024 slots of 16 components 38.5 / 40.0.
 constexpr int64_t kWideSlots = 512;
 
 // waves per SIMD the E-step needs: the plain-sum EM pass fits five (96 registers), which
@@ -533,7 +536,8 @@ constexpr int kWideBlocks = kTreeTop / kSumBlock;
 // records, 33.4 / 34.5; 20 records 37.3 / 36.9; 39 records 49.3 / 46.0; 78 records 69.8 / 61.5;
 // 256 cells 51.7 / 52.5, 61.8 / 61.0, 102 / 99 and 181 / 174. Small cells lose up to 1.2 us
 // where no bound tells them apart from one large cell among small ones, which the wide form
-// is for (one of 300,000 samples among 256: 55 us where the packed form took 74).
+// is for (one of 300,000 samples among 256 an iteration takes 41 us, 55 before this form and
+// the tree's loads in flight).
 constexpr int kWideCells = 256;  // most cells of a launch
 
 template <int G, typename RT>
