@@ -53,6 +53,18 @@ constexpr int lanes_rounds(int64_t nq, int S, int ns)
     return nqr;
 }
 
+// Whether a product pdf call stages the BSDF components of kStagedQueries queries per wave
+// pass. It needs passes enough to hide a second chain of loads and to even out the last
+// ones, which a query's directions lengthen: time against the unstaged kernel, worst and best
+// of 1 to 16 directions per query in random order and in that of the cells, at 131,072
+// queries of 16 components 0.96 to 1.15, at 262,144 0.88 to 1.02, at 400,000 0.90 to 1.02,
+// at 1.5 M 0.82 to 0.85; of 32 components 0.91 to 1.14, 0.86 to 1.01, 0.85 to 1.01 and 0.80 to
+// 0.84; of 64 (32 rounds a pass) 0.94 to 1.25, 0.90 to 1.35, 0.89 to 0.94 and 0.79 to 0.80. Of
+// up to 8 components the lanes that rotate in vain are few: 8 take 0.94 to 1.08 from
+// 262,144 queries on, 4 take 0.97 to 1.11, so these never stage.
+constexpr int kStagedQueries = 32, kStagedGroup = 16;
+constexpr bool staged_pdf(int G, int64_t nq) { return G >= kStagedGroup && nq >= (G == 64 ? 400000 : 262144); }
+
 // The chunks (work items) of a leaf of a tree refinement: `count` records, up to 2^31 - 1,
 // in chunks of at most `most` (a multiple of 64), all of one size, a multiple of 64, but the
 // last, which takes what is left. Nothing here may add to a count before it divides: a leaf

@@ -783,14 +783,9 @@ __global__ __launch_bounds__(64 * kProdWpb) void product_sample_lanes_kernel(
 // The pdf is bound by vector issue: 657 instructions per wave and four queries with one
 // direction, of which the rotation of all 16 lanes' BSDF components, two of them kept, and
 // the broadcast of these two take about 110. Staged they are shared by 32 queries: 2 M
-// queries of K = Kb = 16 take 485-510 us instead of 585-620. It needs calls that give every
-// SIMD four waves of that many, to hide the second chain of loads: 131,072 queries are level
-// (draws and pdf 86 us), with passes of 16 queries 60,000 lose 2% and 33,000 13%.
+// queries of K = Kb = 16 take 485-510 us instead of 585-620. Calls that take it: staged_pdf.
 // Draws do not stage: their pairs' LDS leaves fewer waves then (60,000 queries of 4 draws 8%
 // slower, 2 M no faster).
-constexpr int kStagedQueries = 32;
-constexpr int64_t kStagedCall = 131072;
-
 template <int G>
 __global__ __launch_bounds__(256) void product_pdf_kernel(
     const float* __restrict__ table, int C, int K, const float* __restrict__ qpos, const int32_t* __restrict__ qcell,
@@ -907,10 +902,11 @@ extern "C" int sdmm_product_pdf(const float* table, int32_t n_cells, int32_t K, 
     if (!qpos || !qcell || !bpar || !bcell || !frames || !dirs || !pdf_out) return SDMM_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K > Kb ? K : Kb);
-    if (nq >= kStagedCall)
-        SDMM_DISPATCH_G(G, (product_pdf_staged_kernel<g><<<grid_for(nq, kStagedQueries), 256, 0, s>>>(
-                               table, n_cells, K, qpos, qcell, btable, n_bsdf, Kb, bpar, bcell, frames, nq, nd, dirs,
-                               pdf_out)))
+    if (staged_pdf(G, nq))
+        SDMM_DISPATCH_G(G, if constexpr (g >= kStagedGroup)(
+                               product_pdf_staged_kernel<g><<<grid_for(nq, kStagedQueries), 256, 0, s>>>(
+                                   table, n_cells, K, qpos, qcell, btable, n_bsdf, Kb, bpar, bcell, frames, nq, nd,
+                                   dirs, pdf_out)))
     else
         SDMM_DISPATCH_G(G, (product_pdf_kernel<g><<<grid_for(nq, 64 / g), 256, 0, s>>>(
                            table, n_cells, K, qpos, qcell, btable, n_bsdf, Kb, bpar, bcell, frames, nq, nd, dirs,

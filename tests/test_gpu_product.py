@@ -294,3 +294,40 @@ def test_large_product_calls_equal_their_parts(dev, K, Kb, nq):
     for j, axis in enumerate((1, 0, 0)):
         assert dev.equal(whole[j], dev.cat([p[j] for p in parts], dim=axis)), j
     dev.testing.assert_close(whole[3], dev.cat([p[3] for p in parts]), rtol=PDF_RTOL, atol=2e-6)
+
+
+@pytest.mark.parametrize("K,Kb,nq", [(16, 16, 262144), (9, 3, 262173), (3, 32, 262145), (64, 2, 400003)])
+def test_staged_product_pdfs_of_several_directions(dev, K, Kb, nq):
+    """Calls that stage the BSDF components of 32 queries per wave pass (the size where that
+    begins and ragged last passes), three directions per query, queries in arbitrary order
+    with indices out of range, against the same queries in parts too small for it. The two
+    forms take the same steps; the compiler may contract them differently (a few FP32
+    roundings of a pair's covariance and quadratic form, relative 1e-6 times cond(S), up to
+    1e2), so the tolerance against the oracle holds between them, 2e-6 for values near 0."""
+    print("case: staged product pdfs", K, Kb, nq, flush=True)
+    from paper_2111_13094_amd import sdmm
+    C, CB, nd = 12, 2, 3
+    rng = np.random.default_rng(K + nq)
+    lo = rng.random((C, 3))
+    mix = synth.initial_mixtures(lo, np.full((C, 3), 0.3), K)
+    qcell = rng.integers(0, C, nq).astype(np.int32)
+    qpos = (lo[qcell] + 0.3 * rng.random((nq, 3))).astype(np.float32)
+    bpar, bcell, F = synth.bsdf_queries(5, nq, CB)
+    qcell[rng.integers(0, nq, 5)] = C
+    bcell[rng.integers(0, nq, 5)] = -1
+    sc = dict(C=C, K=K, mix=mix, CB=CB, Kb=Kb, bmix=synth.bsdf_mixtures(6, CB, Kb), qpos=qpos, qcell=qcell,
+              bpar=bpar.astype(np.float32), bcell=bcell, F=F.astype(np.float32))
+    g = _gpu_inputs(dev, sc)
+    d = rng.normal(size=(nq * nd, 3))
+    d = dev.from_numpy(np.ascontiguousarray((d / np.linalg.norm(d, axis=1, keepdims=True)).T.astype(np.float32))).cuda()
+
+    def call(a, b):
+        q = [g[k][..., a:b].contiguous() for k in ("qpos", "qcell", "bpar", "bcell", "frames")]
+        return sdmm.product_pdf(g["table"], C, K, q[0], q[1], g["btable"], CB, Kb, q[2], q[3], q[4],
+                                d[:, a * nd:b * nd].contiguous())
+
+    whole = call(0, nq)
+    parts = dev.cat([call(a, min(nq, a + 49999)) for a in range(0, nq, 49999)])
+    assert (whole.reshape(nq, nd)[dev.from_numpy((qcell == C) | (bcell < 0)).cuda()] == 0).all()
+    dev.testing.assert_close(whole, parts, rtol=PDF_RTOL, atol=2e-6)
+    print("unequal bits:", int((whole != parts).sum()), "of", whole.numel(), flush=True)

@@ -52,6 +52,14 @@ def test_one_separate_draw_keeps_the_group_kernel(rules):
     assert got == [int(2 <= ns and S * ns <= 64 and t <= 4 << 20) for S, ns, t in cases]
 
 
+def test_staged_product_pdfs(rules):
+    """The product pdf stages from 262144 queries on (400000 of more than 32 components), never
+    for groups of fewer than 16 component lanes."""
+    cases = [(G, nq) for G in (4, 8, 16, 32, 64) for nq in (1, 131072, 262143, 262144, 399999, 400000, 1 << 40)]
+    got = rules([f"staged_pdf({G}, v * {nq}LL)" for G, nq in cases])
+    assert got == [int(G >= 16 and nq >= (400000 if G == 64 else 262144)) for G, nq in cases]
+
+
 def test_batches_cover_every_draw(rules):
     """The batches of G draws cover all ns draws and their first draw's index stays in 32
     bits, up to the largest ns."""
