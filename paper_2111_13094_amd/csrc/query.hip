@@ -147,6 +147,10 @@ __device__ __forceinline__ void sample_one(const float* T, bool usable, float wk
     }
 }
 
+// A conditioned mean, moved as one 8-byte value. The arrays are the caller's and floats, so
+// only 4-byte aligned, which the memory instructions accept.
+typedef float CondMean __attribute__((ext_vector_type(2), aligned(4)));
+
 // ---------------------------------------------------------------------------------
 // kernels: the loop trip count is uniform per wave so every group reaches the DPP steps
 // ---------------------------------------------------------------------------------
@@ -188,8 +192,7 @@ __global__ __launch_bounds__(256) void condition_kernel(const float* __restrict_
             const float wk = cond_weight<G>(lw);
             if (q < nq && comp < K) {
                 cw[q * K + comp] = wk;
-                reinterpret_cast<float2*>(cm)[q * K + comp] =
-                    usable[u] ? make_float2(m0, m1) : make_float2(0.0f, 0.0f);
+                reinterpret_cast<CondMean*>(cm)[q * K + comp] = usable[u] ? CondMean{m0, m1} : CondMean{0.0f, 0.0f};
             }
         }
     }
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(256) void pdf_kernel(const float* __restrict__ tabl
     for (int64_t p0 = wave * (S * U); p0 < np; p0 += nwaves * (S * U)) {
         int qc[U];
         float w[U][3], T[U][kCond], wk[U];
-        float2 m[U];
+        CondMean m[U];
         bool usable[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(256) void pdf_kernel(const float* __restrict__ tabl
             const int64_t q = query_of(p, nd, small);
             qc[u] = qcell[q];
             wk[u] = cw[q * K + kk];
-            m[u] = reinterpret_cast<const float2*>(cm)[q * K + kk];
+            m[u] = reinterpret_cast<const CondMean*>(cm)[q * K + kk];
 #pragma unroll
             for (int d = 0; d < 3; ++d) w[u][d] = dirs[d * np + p];
         }
@@ -470,7 +473,7 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(
                 float m0, m1, wk;
                 if constexpr (Given) {
                     wk = (usable && comp < K) ? cw[qq * K + kk] : 0.0f;
-                    const float2 m = reinterpret_cast<const float2*>(cm)[qq * K + kk];
+                    const CondMean m = reinterpret_cast<const CondMean*>(cm)[qq * K + kk];
                     m0 = m.x;
                     m1 = m.y;
                 } else {

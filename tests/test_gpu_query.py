@@ -302,3 +302,30 @@ def test_very_many_draws_of_one_query(dev, K, ns):
         assert e[2].any()
         for got, want in ((d[:, sl], e[0]), (p[sl], e[1]), (v[sl], e[2]), (c[sl], e[3])):
             assert dev.equal(got, want)
+
+
+@pytest.mark.parametrize("ns", [1, 4, 70])
+def test_conditioned_means_at_a_4_byte_address(dev, fitted, ns):
+    """cond_m is an array of floats: at an address that is no multiple of 8 the pdf and the
+    draws are those of the same array at one that is, and the conditioning written there is
+    the same."""
+    print("case: cond_m at a 4-byte address, draws", ns, flush=True)
+    from paper_2111_13094_amd import sdmm
+    import ctypes as C
+    wl, mix, qpos, qcell = fitted
+    n_cells, K, nq = wl["grid"].n_cells, 16, qcell.size
+    table, qp, qc, cw, cm = _gpu_cond(dev, mix, n_cells, K, qpos, qcell)
+    off = dev.empty(cm.numel() + 1, dtype=dev.float32, device="cuda")[1:].view(nq, K, 2)
+    assert off.data_ptr() % 8 == 4 and cm.data_ptr() % 8 == 0
+    off.fill_(-1.0)
+    cw2 = dev.empty_like(cw)
+    p = lambda t: C.c_void_p(t.data_ptr())
+    assert sdmm.lib().sdmm_condition(p(table), n_cells, K, p(qp), p(qc), nq, p(cw2), p(off),
+                                     C.c_void_p(dev.cuda.current_stream().cuda_stream)) == 0
+    assert dev.equal(cw2, cw) and dev.equal(off, cm)
+    d = dev.randn(3, nq, generator=dev.Generator(device="cuda").manual_seed(1), device="cuda")
+    d = (d / d.norm(dim=0)).contiguous()
+    assert dev.equal(sdmm.pdf(table, n_cells, K, qc, cw, off, d, 1), sdmm.pdf(table, n_cells, K, qc, cw, cm, d, 1))
+    for a, b in zip(sdmm.sample(table, n_cells, K, qc, cw, off, ns, seed=5, with_comp=True),
+                    sdmm.sample(table, n_cells, K, qc, cw, cm, ns, seed=5, with_comp=True)):
+        assert dev.equal(a, b)
