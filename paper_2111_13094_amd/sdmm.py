@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
 
 import torch
 
@@ -200,20 +201,48 @@ def new_state(n_cells: int, K: int, device="cuda") -> dict:
             "step": torch.zeros(n_cells, dtype=torch.int32, device=device)}
 
 
-_ws_cache: dict = {}
-
-
 def workspace_bytes(n_cells: int, K: int, n_samples: int, opts: FitOpts) -> int:
     return int(lib().sdmm_fit_workspace_size(n_cells, K, n_samples, C.byref(opts)))
 
 
-def _workspace(nbytes: int, device) -> torch.Tensor:
-    key = (str(device),)
-    ws = _ws_cache.get(key)
+# Workspaces of calls that pass none: one per host thread, device and stream, since two calls
+# that are not ordered by a stream would write the same records and control words. The calls
+# of one stream are ordered on the device, those of one thread on the host (two threads on
+# one stream could enqueue their kernels in turn). A thread keeps the _WS_KEPT it used last.
+# A buffer is allocated on the stream it is used on, so one that is dropped or replaced is
+# handed out again only in that stream's order, and goes back when its thread ends.
+_WS_KEPT = 4
+_ws = threading.local()
+
+
+def _new_workspace(nbytes: int, device) -> torch.Tensor:
+    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+
+
+def _kept_workspace(nbytes: int, device, stream: int) -> torch.Tensor:
+    """The calling thread's workspace for the stream of this raw handle, which is current."""
+    kept = _ws.__dict__.setdefault("kept", {})
+    key = (device, stream)
+    ws = kept.pop(key, None)
     if ws is None or ws.numel() < nbytes:
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-        _ws_cache[key] = ws
+        ws = _new_workspace(nbytes, device)
+    kept[key] = ws  # last in the order of use
+    if len(kept) > _WS_KEPT:
+        del kept[next(iter(kept))]
     return ws
+
+
+def _workspace(nbytes: int, device, stream=None) -> torch.Tensor:
+    if device.type != "cuda":  # refused with the tensors it came from
+        return _new_workspace(nbytes, device)
+    if stream is not None:
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+        with torch.cuda.stream(stream):
+            return _workspace(nbytes, device)
+    if torch.cuda.is_current_stream_capturing():  # the graph's own memory, which lives as long as it
+        return _new_workspace(nbytes, device)
+    return _kept_workspace(nbytes, device, _stream())
 
 
 def fit_mixtures(cell_offsets: torch.Tensor, samples: torch.Tensor, mix: dict, state: dict, opts: FitOpts,
@@ -236,7 +265,7 @@ def fit_mixtures(cell_offsets: torch.Tensor, samples: torch.Tensor, mix: dict, s
         nbytes = workspace_bytes(n_cells, K, N, opts)
         if opts.flags & FLAG_CARRY_MIRRORS:
             raise ValueError("FLAG_CARRY_MIRRORS needs a workspace that the caller keeps between calls")
-        workspace = _workspace(nbytes, samples.device)
+        workspace = _workspace(nbytes, samples.device, stream)
     m = _mixtures(mix, n_cells, K)
     st = _state_ptrs(state, n_cells, K)
     rc = lib().sdmm_fit_mixtures(_ptr(cell_offsets, torch.int64), _ptr(samples, torch.float32), N, C.byref(m),
@@ -450,7 +479,7 @@ def tree_refine(t: dict, samples, split_threshold, mix: dict, state: dict, K, mi
     sorted_ = torch.empty_like(samples)
     offsets = torch.empty(t["max_leaves"] + 1, dtype=torch.int64, device=dev)
     if workspace is None:
-        workspace = _workspace(lib().sdmm_tree_workspace_size(N, t["max_leaves"]), dev)
+        workspace = _workspace(lib().sdmm_tree_workspace_size(N, t["max_leaves"]), dev, stream)
     m = _mixtures(mix, t["max_leaves"], K)
     st = _state_ptrs(state, t["max_leaves"], K)
     nl, status = C.c_int32(0), C.c_int32(0)
@@ -477,7 +506,7 @@ def fit_grad(cell_offsets, samples, mix, opts: FitOpts, workspace=None, stream=N
            "L": torch.empty(n_cells, K, 15, dtype=torch.float64, device=dev),
            "status": torch.empty(n_cells, dtype=torch.int32, device=dev)}
     if workspace is None:
-        workspace = _workspace(workspace_bytes(n_cells, K, N, opts), dev)
+        workspace = _workspace(workspace_bytes(n_cells, K, N, opts), dev, stream)
     m = _mixtures(mix, n_cells, K)
     rc = lib().sdmm_fit_grad(_ptr(cell_offsets, torch.int64), _ptr(samples, torch.float32), N, C.byref(m),
                              C.byref(opts), _ptr(out["F"], torch.float64), _ptr(out["alpha"], torch.float64),

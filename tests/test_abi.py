@@ -230,3 +230,44 @@ def test_noalloc_entry_rejects_on_the_host(lib):
     assert lib.sdmm_fit_workspace_size(4, 16, n, C.byref(o)) > sdmm.NOALLOC_SCRATCH_BYTES
     assert lib.sdmm_fit_mixtures_noalloc(p, p, n, C.byref(m), C.byref(st), C.byref(o), p, None) == -3
     assert lib.sdmm_fit_mixtures_noalloc(None, p, 100, C.byref(m), C.byref(st), C.byref(o), p, None) == -1
+
+
+def test_workspaces_are_not_shared_between_streams_or_threads():
+    """Calls without a workspace on different streams, or from different threads, never get
+    the same buffer; calls of one thread on one stream do; a thread keeps a bounded number and
+    gives them back at its end."""
+    import threading
+    import weakref
+
+    import torch
+    from paper_2111_13094_amd import sdmm
+    dev = torch.device("cpu")
+    out = {}
+
+    def use():
+        a = sdmm._kept_workspace(1000, dev, 1)
+        assert sdmm._kept_workspace(500, dev, 1) is a and a.numel() >= 1000
+        b = sdmm._kept_workspace(1000, dev, 2)
+        bigger = sdmm._kept_workspace(2000, dev, 1)
+        assert b is not a and bigger is not a and bigger.numel() >= 2000
+        assert sdmm._kept_workspace(1000, dev, 2) is b
+        for stream in range(3, 3 + sdmm._WS_KEPT):
+            sdmm._kept_workspace(1000, dev, stream)
+        assert len(sdmm._ws.kept) == sdmm._WS_KEPT
+        assert sdmm._kept_workspace(1000, dev, 2) is not b  # not used for longest
+        out[threading.current_thread().name] = sdmm._kept_workspace(1000, dev, 1)
+
+    def gone():
+        use()
+        out["ref"] = [weakref.ref(t) for t in sdmm._ws.kept.values()]
+
+    use()
+    threads = [threading.Thread(target=use, name=f"t{i}") for i in range(2)] + [threading.Thread(target=gone, name="g")]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    ws = [out[k] for k in out if k != "ref"]
+    assert len(ws) == 4 and len({t.data_ptr() for t in ws}) == 4
+    ws = out = {k: v for k, v in out.items() if k == "ref"}
+    assert all(r() is None for r in out["ref"])

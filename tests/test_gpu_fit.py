@@ -242,6 +242,41 @@ def test_graph_replays_match_eager(dev, orc):
             assert dev.equal(ge[k], gg[k]), (rep, k)
 
 
+def test_captured_call_keeps_its_own_workspace(dev, orc):
+    """A fit without a workspace captured into a graph: replays between eager fits that need
+    larger workspaces, and tensors that would take over any memory given back, equal the same
+    fits made eagerly."""
+    print("case: captured fit without a workspace", flush=True)
+    from paper_2111_13094_amd import sdmm
+    wl, b = _single(4000)
+    big = synth.workload_batch(synth.workload("cells4k", scale=64 / 4096))
+    off, smp = dev.from_numpy(b.offsets).cuda(), dev.from_numpy(b.samples).cuda()
+    mix0 = synth.initial_mixtures(wl["box_lo"], wl["box_size"], 16)
+    o = sdmm.default_opts(16, eta=0.1)
+    ge, se = to_torch(mix0), state_to_torch(orc.new_state(1, 16))
+    gg, sg = to_torch(mix0), state_to_torch(orc.new_state(1, 16))
+    status = dev.zeros(1, dtype=dev.int32, device="cuda")
+    sdmm.fit_mixtures(off, smp, ge, se, o)  # one eager step on both sides
+    sdmm.fit_mixtures(off, smp, gg, sg, o)
+    dev.cuda.synchronize()
+    graph = dev.cuda.CUDAGraph()
+    with dev.cuda.graph(graph):
+        sdmm.fit_mixtures(off, smp, gg, sg, o, status=status)
+    wl2 = synth.workload("cells4k", scale=64 / 4096)
+    C = wl2["grid"].n_cells
+    for rep in range(4):
+        gm, st = to_torch(synth.initial_mixtures(wl2["box_lo"], wl2["box_size"], 16)), sdmm.new_state(C, 16)
+        _gpu_fit(dev, big, gm, st)
+        junk = [dev.full((n,), 7.0, device="cuda") for n in (1 << 10, 1 << 16, 1 << 20, 1 << 23)]
+        graph.replay()
+        sdmm.fit_mixtures(off, smp, ge, se, o)
+        dev.cuda.synchronize()
+        assert int(status[0]) == 0 and all(bool((j == 7.0).all()) for j in junk)
+        for a, c in ((ge, gg), (se, sg)):
+            for k in a:
+                assert dev.equal(a[k], c[k]), (rep, k)
+
+
 def test_cell_independence_bitwise(dev, orc):
     print("case: cells fitted together vs alone", flush=True)
     wl = synth.workload("cells4k", scale=27 / 4096)

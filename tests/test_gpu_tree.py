@@ -353,3 +353,68 @@ def test_refine_of_one_leaf(dev, orc, n, c):
     t_gpu, t_orc, g, o = _refine_both(dev, orc, _samples(n, 41), c, 4, depth=0, seed=42, n_init=1)
     assert (t_orc.n_leaves == 1) == (n <= c)
     _assert_refine_equal(t_gpu, t_orc, g, o)
+
+
+def test_calls_on_two_streams_and_threads_do_not_share_a_workspace(dev, orc):
+    """Refinements and fits without a workspace of their own, queued on two streams by one
+    thread and on two more by two threads, against the same calls one after the other."""
+    print("case: refinements and fits on four streams", flush=True)
+    import threading
+    from paper_2111_13094_amd import sdmm
+    rng = np.random.default_rng(50)
+    fits = []
+    for i in range(4):
+        lo = rng.random((40, 3))
+        b = synth.make_batch(51 + i, np.full(40, 700 + 300 * i), lo, np.full((40, 3), 0.2), synth.planted_lobes(5))
+        fits.append((dev.from_numpy(b.offsets).cuda(), dev.from_numpy(b.samples).cuda(),
+                     synth.initial_mixtures(lo, np.full((40, 3), 0.2), K)))
+    smp = [dev.from_numpy(_samples(30000 + 5000 * i, 60 + i)).cuda() for i in range(4)]
+
+    def inputs():
+        out = []
+        for i in range(4):
+            t = sdmm.new_tree(256)
+            sdmm.tree_init(t, 1, [0, 0, 0], [1, 1, 1])
+            mix, st = _store(256)
+            out.append((t, to_torch(mix), state_to_torch(st), to_torch(fits[i][2]), sdmm.new_state(40, K)))
+        dev.cuda.synchronize()
+        return out
+
+    keep = []  # what calls on other streams than the current one still write
+
+    def calls(i, x, **stream):
+        t, mix, st, fm, fs = x[i]
+        for _ in range(3):
+            keep.append(sdmm.fit_mixtures(fits[i][0], fits[i][1], fm, fs, sdmm.default_opts(K, iters=4), **stream))
+        return sdmm.tree_refine(t, smp[i], 1500, mix, st, K, **stream)
+
+    ref, x = [], inputs()
+    for i in range(4):
+        ref.append(calls(i, x))
+        dev.cuda.synchronize()
+    first, y, got = inputs(), inputs(), [None] * 4
+    streams = [dev.cuda.Stream() for _ in range(4)]
+
+    def by_argument(which):
+        for i in which:  # interleaved
+            keep.append(sdmm.fit_mixtures(fits[i][0], fits[i][1], *first[i][3:], sdmm.default_opts(K, iters=4),
+                                          stream=streams[i]))
+        for i in which:
+            got[i] = calls(i, y, stream=streams[i])
+
+    def by_context(i):
+        with dev.cuda.stream(streams[i]):
+            got[i] = calls(i, y)
+
+    threads = [threading.Thread(target=by_context, args=(i,)) for i in (2, 3)]
+    for t in threads:
+        t.start()
+    by_argument([0, 1])
+    for t in threads:
+        t.join()
+    dev.cuda.synchronize()
+    for i in range(4):
+        assert dev.equal(got[i][0], ref[i][0]) and dev.equal(got[i][1], ref[i][1]) and got[i][2:] == ref[i][2:], i
+        for a, b in zip(x[i][3:], y[i][3:]):
+            for k in a:
+                assert dev.equal(a[k], b[k]), (i, k)
