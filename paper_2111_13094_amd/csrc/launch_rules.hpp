@@ -39,9 +39,20 @@ constexpr int draw_batches(int ns, int G) { return ns / G + (ns % G != 0 ? 1 : 0
 
 constexpr int kLanesRounds = 4;  // most rounds of S queries per pass of the query kernels
 
-// wave groups below which a query launch keeps one round per wave (four waves per SIMD, so
+// wave groups below which the passes of a launch take fewer rounds (four waves per SIMD, so
 // that a small call spreads out)
 constexpr int64_t kFewGroups = 4096;
+
+// Whether the condition and pdf kernels take kRounds rounds of S items per wave pass, all their
+// loads ahead (else one). That pays where the rows miss the L2: 16 components, 524,288
+// queries in random order over 8192 cells 71.4 against 73.2 us, over 2048 35.0 against 37.2; in
+// the order of the cells it is level (35.1 against 34.8). Below 16 wave groups per SIMD the
+// longer passes even out badly (pdf of 85,000 to 110,000 directions up to 10% slower), and
+// the pdf of groups of 4 lanes loses up to 7% at any size.
+constexpr int kRounds = 4;
+constexpr int64_t kRoundsGroups = 16384;
+constexpr bool condition_in_rounds(int S, int64_t nq) { return nq >= kRoundsGroups * S * kRounds; }
+constexpr bool pdf_in_rounds(int S, int64_t items) { return S <= 8 && items >= kRoundsGroups * S * kRounds; }
 
 // rounds of the query kernels' passes: as many as fill the lanes, at most kLanesRounds (more
 // take the LDS of one wave less per SIMD: 4% slower in path order), fewer where the call is

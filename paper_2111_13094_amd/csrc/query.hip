@@ -601,8 +601,6 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(
     }
 }
 
-constexpr int kRounds = 4;  // rounds per pass of the condition and pdf kernels
-
 }  // namespace sdmm
 
 using namespace sdmm;
@@ -627,7 +625,7 @@ extern "C" int sdmm_condition(const float* table, int32_t n_cells, int32_t K, co
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K);
     const int S = 64 / G;
-    if (nq >= kFewGroups * S * kRounds)
+    if (condition_in_rounds(S, nq))
         SDMM_DISPATCH_G(G, (condition_kernel<g, kRounds><<<grid_for(nq, S * kRounds), 256, 0, s>>>(
                                table, n_cells, K, qpos, qcell, nq, cond_w, cond_m)))
     else
@@ -646,9 +644,10 @@ extern "C" int sdmm_pdf(const float* table, int32_t n_cells, int32_t K, const in
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int G = group_for(K);
     const int S = 64 / G;
-    if (nq * nd >= kFewGroups * S * kRounds)
-        SDMM_DISPATCH_G(G, (pdf_kernel<g, kRounds><<<grid_for(nq * nd, S * kRounds), 256, 0, s>>>(
-                               table, n_cells, K, qcell, nq, cond_w, cond_m, nd, dirs, pdf_out)))
+    if (pdf_in_rounds(S, nq * nd))
+        SDMM_DISPATCH_G(G, if constexpr (pdf_in_rounds(64 / g, INT64_MAX))(
+                               pdf_kernel<g, kRounds><<<grid_for(nq * nd, S * kRounds), 256, 0, s>>>(
+                                   table, n_cells, K, qcell, nq, cond_w, cond_m, nd, dirs, pdf_out)))
     else
         SDMM_DISPATCH_G(G, (pdf_kernel<g, 1><<<grid_for(nq * nd, S), 256, 0, s>>>(table, n_cells, K, qcell, nq, cond_w,
                                                                                   cond_m, nd, dirs, pdf_out)))

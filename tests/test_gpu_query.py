@@ -329,3 +329,31 @@ def test_conditioned_means_at_a_4_byte_address(dev, fitted, ns):
     for a, b in zip(sdmm.sample(table, n_cells, K, qc, cw, off, ns, seed=5, with_comp=True),
                     sdmm.sample(table, n_cells, K, qc, cw, cm, ns, seed=5, with_comp=True)):
         assert dev.equal(a, b)
+
+
+@pytest.mark.parametrize("K,nq,nd", [(16, 262144, 1), (16, 262157, 2), (5, 524295, 1), (33, 65539, 3), (3, 1048590, 1)])
+def test_calls_of_several_rounds_equal_their_parts(dev, K, nq, nd):
+    """Conditioning and pdf of calls that take four rounds per wave pass (the size where that
+    begins, ragged last passes, several directions), on queries in arbitrary order with some
+    cells out of range, bit for bit as the same queries in parts too small for it."""
+    print("case: rounds of condition and pdf", K, nq, nd, flush=True)
+    from paper_2111_13094_amd import sdmm
+    C = 40
+    rng = np.random.default_rng(K)
+    lo = rng.random((C, 3))
+    mix = synth.initial_mixtures(lo, np.full((C, 3), 0.3), K)
+    qcell = rng.integers(0, C, nq).astype(np.int32)
+    qpos = (lo[qcell] + 0.3 * rng.random((nq, 3))).astype(np.float32)
+    qcell[rng.integers(0, nq, 5)] = -1
+    qcell[rng.integers(0, nq, 5)] = C
+    table, qp, qc, cw, cm = _gpu_cond(dev, mix, C, K, qpos, qcell)
+    d = dev.randn(3, nq * nd, generator=dev.Generator(device="cuda").manual_seed(K), device="cuda")
+    d = (d / d.norm(dim=0)).contiguous()
+    p = sdmm.pdf(table, C, K, qc, cw, cm, d, nd)
+    step = 15013
+    for a in range(0, nq, step):
+        b = min(nq, a + step)
+        w, m = sdmm.condition(table, C, K, qp[:, a:b].contiguous(), qc[a:b].contiguous())
+        assert dev.equal(w, cw[a:b]) and dev.equal(m, cm[a:b]), a
+        e = sdmm.pdf(table, C, K, qc[a:b].contiguous(), w, m, d[:, a * nd:b * nd].contiguous(), nd)
+        assert dev.equal(e, p[a * nd:b * nd]), a

@@ -52,6 +52,16 @@ def test_one_separate_draw_keeps_the_group_kernel(rules):
     assert got == [int(2 <= ns and S * ns <= 64 and t <= 4 << 20) for S, ns, t in cases]
 
 
+def test_rounds_of_the_separate_calls(rules):
+    """Four rounds per pass from 16384 wave groups of that many on; the pdf of groups of 4
+    lanes takes one."""
+    cases = [(S, n) for S in (1, 2, 4, 8, 16) for n in (1, 65535 * S, 65536 * S - 1, 65536 * S, 1 << 50)]
+    got = rules([f"condition_in_rounds({S}, v * {n}LL)" for S, n in cases])
+    assert got == [int(n >= 65536 * S) for S, n in cases]
+    got = rules([f"pdf_in_rounds({S}, v * {n}LL)" for S, n in cases])
+    assert got == [int(S <= 8 and n >= 65536 * S) for S, n in cases]
+
+
 def test_staged_product_pdfs(rules):
     """The product pdf stages from 262144 queries on (400000 of more than 32 components), never
     for groups of fewer than 16 component lanes."""
