@@ -418,3 +418,14 @@ def test_calls_on_two_streams_and_threads_do_not_share_a_workspace(dev, orc):
         for a, b in zip(x[i][3:], y[i][3:]):
             for k in a:
                 assert dev.equal(a[k], b[k]), (i, k)
+
+
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 8191, 8192, 12289])
+@pytest.mark.parametrize("c", [4096, 511, 40])
+def test_refine_about_one_chunk(dev, orc, n, c):
+    """One leaf of a chunk (4096 records, 8 waves of 512) less one, exactly, and plus one, and
+    of two and three chunks, refined in several rounds down to leaves within one wave."""
+    print("case: chunk", n, c, flush=True)
+    t_gpu, t_orc, g, o = _refine_both(dev, orc, _samples(n, 71), c, 1024, depth=0, seed=72, n_init=1)
+    assert np.diff(o[1]).max() <= c
+    _assert_refine_equal(t_gpu, t_orc, g, o)
