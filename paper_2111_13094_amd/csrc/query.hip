@@ -502,6 +502,8 @@ __global__ __launch_bounds__(256) void cond_sample_pdf_lanes_kernel(
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // this wave's LDS writes are done
         // B: one draw per lane
         {
+            // the generator's round keys and the channel strides are formed here, by scalar
+            // instructions, instead of being held across the loop in scalar registers that spill
             uint64_t key = seed;
             int64_t ndo = nd;
             asm volatile("" : "+s"(key), "+s"(ndo));

@@ -535,10 +535,10 @@ __device__ __forceinline__ uint64_t digit_peers(int digit, bool valid, int bits)
 //
 // With up to kStageBins bins the records go to LDS in their sorted order first (positions,
 // then directions and weights, through the same 64 KB), and consecutive lanes then write
-// the runs of a digit whole. The traffic is what it has to be (by counters 541 MB read and
-// 562 MB written for 16.6M samples over 512 leaves), so latency sets the time: 16 waves per
-// tile take 243 us, 4 waves with four times the samples each took 428 us (4.4 against 2.5
-// TB/s). Stored as they come, 16 bytes a request, the records take 378 us. With more bins
+// the runs of a digit whole. The traffic is what it has to be (by counters 540 MB read and
+// 532 MB written for 16.6M samples over 512 leaves, 32 bytes each way and the keys), so latency
+// sets the time: 16 waves per tile take 243 us, 4 waves with four times the samples each took
+// 428 us (4.4 against 2.5 TB/s). Stored as they come, 16 bytes a request, the records take 378 us. With more bins
 // a tile's runs are only a record or two long and the rows no longer fit: the records are
 // stored as they come.
 constexpr int kStageBins = 2048;
@@ -781,8 +781,8 @@ __device__ __forceinline__ void block_part(Stat& s, Part* shared, Part* out)
     }
 }
 
-// the records of a thread in a chunk: wave w holds the chunk's records [1024 w, 1024 (w + 1)),
-// lane l of step it record 1024 w + 64 it + l (a record past the end is the last one again)
+// the records of a thread in a chunk: wave w holds the chunk's records [512 w, 512 (w + 1)),
+// lane l of step it record 512 w + 64 it + l (a record past the end is the last one again)
 __device__ __forceinline__ void load_chunk(const float4* __restrict__ p, int32_t n, float4 (&r)[kChunkItems])
 {
     const int first = (threadIdx.x >> 6) * (64 * kChunkItems) + (threadIdx.x & 63);
